@@ -4,6 +4,7 @@
 // of the sweeps are batched GEMMs (k_mgemm.hip).
 #include "common.h"
 #include "kernels.h"
+#include "thinq.h"
 
 namespace peps {
 
@@ -136,12 +137,8 @@ __global__ __launch_bounds__(NT) void k_thinq(const double* X, long long xs, int
     }
 }
 
-// The same factorisation with the matrix in registers: column j belongs to wave j % NW
-// (slot j / NW), its rows i = lane + 64 r (r < RPL) to that wave's lanes, so m <= 64 RPL
-// and n <= NW * SL.  Only the current reflector v_k is shared, through a double-buffered
-// LDS vector (one barrier per step): the owner of column k forms it with wave reductions,
-// every wave applies it to its own trailing columns.  Q is formed in the registers the same
-// way, backwards, and stored with the signs that make diag(R) >= 0.
+// The same factorisation with the matrix in registers (thinq.h).  Q is stored with the signs
+// that make diag(R) >= 0.
 template <int NW, int SL, int RPL>
 __global__ __launch_bounds__(NW * 64) void k_thinq_reg(const double* X, long long xs, int m, int n, double* Q,
                                                        long long qs, long long q_row, long long q_col, double* R,
@@ -160,73 +157,7 @@ __global__ __launch_bounds__(NW * 64) void k_thinq_reg(const double* X, long lon
             a[s][r] = (j < n && i < m) ? Xb[i + (long long)j * m] : 0.0;
         }
     }
-    for (int k = 0; k < n; ++k) {
-        double* v = vbuf[k & 1];
-        if (w == k % NW) {
-            const int sk = k / NW;
-            double x[RPL];
-#pragma unroll
-            for (int s = 0; s < SL; ++s)
-                if (s == sk) {
-#pragma unroll
-                    for (int r = 0; r < RPL; ++r) x[r] = a[s][r];
-                }
-            double ss = 0.0, al = 0.0;
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const int i = lane + 64 * r;
-                if (i > k && i < m) ss += x[r] * x[r];
-                if (i == k) al = x[r];
-            }
-            ss = vq_wsum(ss);
-            al = vq_wsum(al);
-            double tk = 0.0, beta = al, sc = 0.0;
-            if (ss > 0.0) {
-                beta = -copysign(sqrt(al * al + ss), al);
-                tk = (beta - al) / beta;
-                sc = 1.0 / (al - beta);
-            }
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const int i = lane + 64 * r;
-                double vi = 0.0;
-                if (i == k) {
-                    vi = 1.0;
-                    x[r] = beta;
-                } else if (i > k && i < m) {
-                    vi = ss > 0.0 ? x[r] * sc : 0.0;
-                    x[r] = vi;
-                }
-                v[i] = vi;
-            }
-#pragma unroll
-            for (int s = 0; s < SL; ++s)
-                if (s == sk) {
-#pragma unroll
-                    for (int r = 0; r < RPL; ++r) a[s][r] = x[r];
-                }
-            if (lane == 0) tau[k] = tk;
-        }
-        __syncthreads();
-        const double tk = tau[k];
-        if (tk != 0.0) {
-            double vr[RPL];
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) vr[r] = v[lane + 64 * r];
-#pragma unroll
-            for (int s = 0; s < SL; ++s) {
-                const int j = s * NW + w;
-                if (j > k && j < n) {
-                    double d = 0.0;
-#pragma unroll
-                    for (int r = 0; r < RPL; ++r) d += vr[r] * a[s][r];
-                    d = vq_wsum(d) * tk;
-#pragma unroll
-                    for (int r = 0; r < RPL; ++r) a[s][r] -= d * vr[r];
-                }
-            }
-        }
-    }
+    thinq_factor<NW, SL, RPL>(a, m, n, vbuf, tau);
     // signs of diag(R) and R itself
 #pragma unroll
     for (int s = 0; s < SL; ++s) {
@@ -248,43 +179,7 @@ __global__ __launch_bounds__(NW * 64) void k_thinq_reg(const double* X, long lon
             }
         }
     }
-    // Q, backwards: H_k applied to the columns right of k, then column k becomes e_k - tau_k v_k
-    for (int k = n - 1; k >= 0; --k) {
-        double* v = vbuf[k & 1];
-        const double tk = tau[k];
-        if (w == k % NW) {
-            const int sk = k / NW;
-#pragma unroll
-            for (int s = 0; s < SL; ++s)
-                if (s == sk) {
-#pragma unroll
-                    for (int r = 0; r < RPL; ++r) {
-                        const int i = lane + 64 * r;
-                        const double vi = i == k ? 1.0 : (i > k && i < m ? a[s][r] : 0.0);
-                        v[i] = vi;
-                        a[s][r] = i < k ? 0.0 : (i == k ? 1.0 - tk : -tk * vi);
-                    }
-                }
-        }
-        __syncthreads();
-        if (tk != 0.0) {
-            double vr[RPL];
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) vr[r] = v[lane + 64 * r];
-#pragma unroll
-            for (int s = 0; s < SL; ++s) {
-                const int j = s * NW + w;
-                if (j > k && j < n) {
-                    double d = 0.0;
-#pragma unroll
-                    for (int r = 0; r < RPL; ++r) d += vr[r] * a[s][r];
-                    d = vq_wsum(d) * tk;
-#pragma unroll
-                    for (int r = 0; r < RPL; ++r) a[s][r] -= d * vr[r];
-                }
-            }
-        }
-    }
+    thinq_form<NW, SL, RPL>(a, m, n, vbuf, tau);
     double* Qb = Q + (long long)b * qs;
 #pragma unroll
     for (int s = 0; s < SL; ++s) {

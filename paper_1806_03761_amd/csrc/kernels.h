@@ -51,11 +51,15 @@ struct EigArgs {
 };
 size_t eig_scratch_doubles(int mz, int tin, int p, int Dc);
 // wyT != nullptr: the reflectors came from the blocked QR, whose WY blocks (wyT, stride wys
-// per matrix) apply Q to [G; 0] on the matrix cores
+// per matrix) apply Q to [G; 0] on the matrix cores.
+// f32_mode: the call of a float32 or bfloat16 mode, whose next product rounds the factors to
+// float32: there a different rounding of this step, harmless in float64, moves ln|W| by up to
+// 5e-8 relative (measured, 8x8 D = 4), so those modes keep their kernels' bits (pivot Sturm
+// counts, LDS refinement)
 hipError_t launch_eig(const double* V, long long vs, const double* tau, long long ts, const double* G,
                       long long gs, int mz, int r, int tin, int p, int Dc, double* newU, long long us,
                       double* Gout, long long gos, double* scratch, long long ss, int batch,
-                      hipStream_t st, const double* wyT = nullptr, long long wys = 0);
+                      hipStream_t st, const double* wyT = nullptr, long long wys = 0, bool f32_mode = false);
 
 // blocked Householder QR (k_qrb.hip) for matrices beyond the register kernels: panels of
 // qrb_panel_width(m) columns factorised in registers, trailing updates in compact WY form

@@ -597,7 +597,8 @@ public:
             const int mz = t.rho[j] * p;
             KL(timed(PEPS_KC_SVD, Bcur * svd_flops(mz, 0, 1, p, t.tau[j]), [&] {
                 return launch_eig(nullptr, 0, buf(o_tau[0]), 0, buf(o_X[j]), s_X[j], mz, mz, 1, p, Dc,
-                                  Eout.p, Eout.bs, buf(o_G[0]), s_G, buf(o_eig), s_eig, Bcur, st_);
+                                  Eout.p, Eout.bs, buf(o_G[0]), s_G, buf(o_eig), s_eig, Bcur, st_, nullptr, 0,
+                                  ar != Arith::F64);
             }));
         }
         for (int j = Lx - 2; j >= 1; --j) {
@@ -607,7 +608,8 @@ public:
                 const bool blocked = use_qrb(mz, t.K[j + 1]);
                 return launch_eig(buf(o_X[j]), s_X[j], buf(o_tau[j]), s_tau[j], buf(o_G[cur]), s_G, mz,
                                   t.rho[j + 1], t.tau[j + 1], p, Dc, Eout.p, Eout.bs, buf(o_G[cur ^ 1]), s_G,
-                                  buf(o_eig), s_eig, Bcur, st_, blocked ? buf(o_wy[j]) : nullptr, s_wy[j]);
+                                  buf(o_eig), s_eig, Bcur, st_, blocked ? buf(o_wy[j]) : nullptr, s_wy[j],
+                                  ar != Arith::F64);
             }));
             cur ^= 1;
         }

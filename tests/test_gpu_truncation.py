@@ -1,0 +1,68 @@
+"""The truncation kernels at the edges of their blockings, against the oracle.
+
+Decaying boundary spectra (a product state plus a Gaussian PEPS) take every branch of the
+truncation step: the Gram eigenproblem, and the refinement of the kept subspace wherever a kept
+eigenvalue falls below 1e-6 of the largest.  The bounds are those of the float64 path: 1e-10
+relative on ln|W|, 1e-9 on E and on the log-derivatives.
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1806_03761_amd.workloads import Lattice, make_random
+
+pytestmark = pytest.mark.gpu
+
+
+def _weak(lat, batch, seed, eps):
+    A, S = make_random(lat, batch, seed)
+    A = eps * A
+    A[:, :, 0, 0, 0, 0] += np.random.default_rng(seed).uniform(0.5, 1.5, size=(lat.N, 2))
+    return A, S
+
+
+def _peps():
+    import torch
+    from paper_1806_03761_amd import peps
+    assert torch.cuda.is_available()
+    return peps
+
+
+def _dev(*xs):
+    import torch
+    return [torch.from_numpy(x).to("cuda:0") for x in xs]
+
+
+# (Lx, Ly, D, Dc): one per register blocking of the refinement, with kept counts on both sides
+# of a wave's 16 columns and orders that do and do not fill their 16-row chunks
+@pytest.mark.parametrize("shape", [(5, 4, 2, 4), (6, 4, 3, 7), (5, 5, 4, 16), (5, 4, 4, 17), (5, 4, 5, 25),
+                                   (5, 4, 6, 36), (4, 4, 7, 43), (4, 4, 8, 33), (3, 4, 16, 32)])
+@pytest.mark.parametrize("eps", [0.3, 0.02])
+def test_truncation_of_decaying_spectra(shape, eps):
+    Lx, Ly, D, Dc = shape
+    lat = Lattice(Lx, Ly, D, Dc)
+    A, S = _weak(lat, 2, 60 + D, eps)
+    la, sg, e, d, fl = (t.cpu().numpy() for t in _peps().evaluate(*_dev(A, S), lat, "f64", grad_mode=1))
+    for b in range(len(S)):
+        la_o, sg_o, e_o, d_o, fl_o = O.full_path_one(A, lat, S[b])
+        assert fl[b] == 0 and fl_o == 0 and sg[b] == sg_o
+        assert abs(la[b] - la_o) <= 1e-10 * max(1, abs(la_o)), (shape, b, la[b], la_o)
+        assert abs(e[b] - e_o) <= 1e-9 * max(1, abs(e_o)), (shape, b, e[b], e_o)
+        assert np.linalg.norm(d[b] - d_o) <= 1e-9 * np.linalg.norm(d_o), (shape, b)
+
+
+# batches on both sides of every change of the eigenvalue kernel's launch shape (points per
+# eigenvalue, matrices per block, one launch or two): each sample equals its own single call
+@pytest.mark.parametrize("shape,batch", [((4, 4, 2, 4), 3000), ((5, 4, 4, 16), 1500), ((5, 4, 4, 16), 5000),
+                                         ((4, 4, 5, 25), 600), ((4, 3, 6, 36), 300)])
+def test_truncation_independent_of_the_batch(shape, batch):
+    Lx, Ly, D, Dc = shape
+    lat = Lattice(Lx, Ly, D, Dc)
+    A, S = make_random(lat, batch, 70 + D)
+    peps = _peps()
+    Ad, Sd = _dev(A, S)
+    la, sg, fl = peps.log_amplitude(Ad, Sd, lat)
+    for b in (0, 1, 63, batch // 2, batch - 1):
+        l1, s1, f1 = peps.log_amplitude(Ad, Sd[b:b + 1].contiguous(), lat)
+        assert int(f1[0]) == int(fl[b]) == 0 and int(s1[0]) == int(sg[b])
+        assert abs(float(l1[0]) - float(la[b])) <= 1e-10 * max(1.0, abs(float(l1[0])))

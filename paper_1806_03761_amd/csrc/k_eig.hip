@@ -8,15 +8,14 @@
 //
 //   k_eig_prep  one workgroup per matrix: Z = Q G, Gram A, Householder reduction
 //               of A to tridiagonal form (d, e); reflectors kept for later.
-//   k_eig_tri   multisection with Sturm counts for the l-th largest eigenvalue, then
-//               inverse iteration on the tridiagonal matrix (LDL^T recurrences), one lane
-//               per (matrix, eigenvalue).
+//   k_eig_tri   one lane per (matrix, eigenvalue): bisection with Sturm counts for
+//               the l-th largest eigenvalue, then inverse iteration on the
+//               tridiagonal matrix (LDL^T recurrences).
 //   k_eig_fin   one workgroup per matrix: modified Gram-Schmidt (twice) on the t
 //               tridiagonal eigenvectors, back-transformation by the reflectors,
 //               then the new boundary tensor V_t^T and U_t Sigma_t.
 #include "common.h"
 #include "kernels.h"
-#include "thinq.h"
 
 namespace peps {
 
@@ -72,13 +71,11 @@ __host__ __device__ inline EigLayout eig_layout(int mz, int tin, int p, int Dc) 
     if (L.nv < 48 * tri_rb(L.ns)) L.nv = 48 * tri_rb(L.ns);
     L.oW = L.oP + (long long)L.ldx * L.tk;
     L.nm = 0;
-    L.oM = (L.oW + L.nv + 1) / 2 * 2;
+    L.oM = L.oW + L.nv;
     L.oY = L.oM;                                   // refinement: Y (mp x tk) and W (np x tk)
     L.oV = L.oY + (long long)L.mp * L.tk;
-    // (before it, the iterates and pivots of the tridiagonal eigenvectors where they do not
-    // fit LDS: 2 tk rows of ns rounded up to 16, hence the slack)
-    L.oQ = L.oV + (long long)(L.np + 32) * L.tk;   // W blocks of the GEMM application of Q
-    L.total = (L.oQ + 64LL * tin + 1) / 2 * 2;
+    L.oQ = L.oV + (long long)L.np * L.tk;          // W blocks of the GEMM application of Q
+    L.total = L.oQ + 64LL * tin;
     // LDS needs of the two workgroup kernels
     L.lds_prep = (long long)L.ldz * tin + (long long)L.lda * L.ns + 3LL * L.ns + L.nv + 8;
     // k_eig_fin stages X, tau and the eigenvalues; the reflectors and Z stay in global
@@ -812,12 +809,11 @@ __device__ inline double sturm_rcp(double q) {
     return fma(fma(-q, r, 1.0), r, r);
 }
 
-// The float32 modes' form, with Sturm counts by pivots (see launch_eig).
 // Block = mats_per_block matrices x tk eigenvalues x S sub-lanes.  The S sub-lanes of an
 // eigenvalue (aligned, consecutive lanes) evaluate the Sturm count at S interior points
 // of the common interval, which therefore shrinks by S + 1 per step (multisection); all
 // of them then hold the same interval.  Sub-lane 0 runs the inverse iteration.
-__global__ __launch_bounds__(256) void k_eig_tri_piv(EigArgs a, int S, int mats_per_block, int tri_lanes_in_lds) {
+__global__ __launch_bounds__(256) void k_eig_tri(EigArgs a, int S, int mats_per_block, int tri_lanes_in_lds) {
     extern __shared__ double tri_lds[];
     const EigLayout L = eig_layout(a.mz, a.tin, a.p, a.Dc);
     const int n = L.ns, tk = L.tk;
@@ -955,245 +951,6 @@ __global__ __launch_bounds__(256) void k_eig_tri_piv(EigArgs a, int S, int mats_
     if (tri_lanes_in_lds) {
         double* xo = gs + L.oX + (long long)l * L.ldx;
         for (int i = 0; i < n; ++i) xo[i] = x[i * xs];
-    }
-}
-
-// Eigenvalues (PART & 1) and tridiagonal eigenvectors (PART & 2).  Block = mpb matrices x epb
-// eigenvalues x S sub-lanes (bpm blocks cover the tk eigenvalues of a matrix when mpb = 1).
-// The S sub-lanes of an eigenvalue (a power of two, so they lie in one wave) evaluate the
-// Sturm count at S interior points of the common interval, which shrinks by S + 1 per step
-// (multisection); sub-lane 0 then runs the inverse iteration.
-//
-// The matrix is scaled by a power of two to a norm in [1/2, 1).  The count comes from the signs
-// of the leading principal minors p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}: one dependent
-// fma per row and five instructions in all, where the pivots p_i / p_{i-1} cost a reciprocal
-// per row; the exponents are brought back every 8 rows (|p| grows by less than 2.5 per row;
-// the squared couplings are kept above 1e-36, a change of 1e-18 of the norm, so that two
-// consecutive minors cannot both vanish).  The computed minors are those of a matrix within a
-// few eps of the norm, as with the pivots.
-//
-// Both recurrences are bound by instruction issue of their one wave per SIMD: rows are taken
-// 8 at a time from arrays padded to whole chunks (padding rows: d = 4, above every x, and
-// e = 0), the next chunk's loads in flight during the current one.  The 49 launches of an
-// 8x8, D = 4, Dc = 16 amplitude: 6.7 ms with pivots and one row at a time, 3.5 ms so (4096
-// samples), 4.2 and 1.5 ms (one sample); order 216, 256 matrices: 550 and 173 us a launch.
-__host__ __device__ inline int tri_pad(int n) { return (n + 15) / 16 * 16; }
-
-template <int PART, bool LDS>
-__global__ __launch_bounds__(256) void k_eig_tri(EigArgs a, int S, int mpb, int epb, int bpm) {
-    extern __shared__ __align__(16) double tri_lds[];
-    const EigLayout L = eig_layout(a.mz, a.tin, a.p, a.Dc);
-    const int n = L.ns, tk = L.tk, tid = threadIdx.x, nvl = mpb * epb, nP = tri_pad(n), nd = nP + 17;
-    const int grp = blockIdx.x / bpm, part = blockIdx.x % bpm;
-    double2* de = reinterpret_cast<double2*>(tri_lds);            // (d_i, e_{i-1}^2), nd per matrix
-    double* es = tri_lds + 2LL * mpb * nd;                        // e_i, nP + 16 per matrix
-    double* lohi = es + (long long)mpb * (nP + 16);               // Gershgorin bounds, exponent, -
-    double2* xl = reinterpret_cast<double2*>(lohi + 4 * mpb);     // (x, 1 / pivot) of every lane
-    for (int m2 = tid >> 6; m2 < mpb; m2 += blockDim.x >> 6) {
-        const int b2 = grp * mpb + m2, lane = tid & 63;
-        const double* g2 = a.scratch + (long long)(b2 < a.batch ? b2 : 0) * a.ss;
-        double lo = INFINITY, hi = -INFINITY;
-        for (int i = lane; i < n; i += 64) {
-            const double dv = g2[L.oD + i];
-            const double el = ld_or0(i > 0, g2, L.oE + i - 1), er = ld_or0(i + 1 < n, g2, L.oE + i);
-            const double r = fabs(el) + fabs(er);
-            lo = fmin(lo, dv - r);
-            hi = fmax(hi, dv + r);
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            lo = fmin(lo, __shfl_xor(lo, o, 64));
-            hi = fmax(hi, __shfl_xor(hi, o, 64));
-        }
-        const double tn = fmax(fabs(lo), fabs(hi));
-        const int ex = tn > 0.0 && tn < INFINITY ? __builtin_amdgcn_frexp_exp(tn) : 0;
-        for (int i = lane; i < nd; i += 64) {
-            const double dv = ld_or0(i < n, g2, L.oD + i), el = ld_or0(i > 0 && i < n, g2, L.oE + i - 1);
-            const double sl = __builtin_amdgcn_ldexp(el, -ex);
-            de[m2 * nd + i] = make_double2(i < n ? __builtin_amdgcn_ldexp(dv, -ex) : 4.0, fmax(sl * sl, 1e-36));
-            if (i < nP + 16)
-                es[m2 * (nP + 16) + i] = __builtin_amdgcn_ldexp(ld_or0(i + 1 < n, g2, L.oE + i), -ex);
-        }
-        if (lane == 0) {
-            lohi[4 * m2] = __builtin_amdgcn_ldexp(lo, -ex);
-            lohi[4 * m2 + 1] = __builtin_amdgcn_ldexp(hi, -ex);
-            lohi[4 * m2 + 2] = (double)ex;
-        }
-    }
-    __syncthreads();
-    const int mi = tid / (epb * S), le = tid % (epb * S), l = part * epb + le / S, sub = le % S;
-    const int b = grp * mpb + mi;
-    if (mi >= mpb || b >= a.batch || l >= tk) return;
-    double* gs = a.scratch + (long long)b * a.ss;
-    const double2* dm = de + mi * nd;
-    const double* e = es + mi * (nP + 16);
-    double lo = lohi[4 * mi], hi = lohi[4 * mi + 1];
-    const int ex0 = (int)lohi[4 * mi + 2];
-    const double tnorm = fmax(fabs(lo), fabs(hi));
-    double lam;
-    if constexpr ((PART & 1) != 0) {
-        const int kidx = n - 1 - l;   // l-th largest = kidx-th smallest
-        const int lane0 = (tid & 63) - sub;
-        const unsigned long long gmask = ((1ULL << S) - 1ULL) << lane0;
-        const double inv = 1.0 / (double)(S + 1);
-        // to the accuracy the tridiagonal supports (about eps times its norm), so that inverse
-        // iteration separates every eigenvalue the Gram matrix resolves; 64 steps bound S = 1
-        for (int it = 0; it < 64 && hi - lo > 4.5e-16 * tnorm; ++it) {
-            const double h = (hi - lo) * inv;
-            const double x = fma((double)(sub + 1), h, lo);
-            double p0 = 1.0, p1 = dm[0].x - x;
-            unsigned cnt = (unsigned)__double2hiint(p1) >> 31;   // eigenvalues below x = sign changes
-            double2 q0[8], q1[8];
-            const double2* dp = dm + 1;
-            const auto load8 = [&](double2 (&q)[8], const double2* src) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) q[u] = src[u];
-            };
-            const auto rows8 = [&](const double2 (&q)[8]) {
-                unsigned m = (unsigned)__double2hiint(p1) >> 31;   // the signs, newest in bit 0
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const double p2 = fma(q[u].x - x, p1, -(q[u].y * p0));
-                    m = __builtin_amdgcn_alignbit(m, (unsigned)__double2hiint(p2), 31);
-                    p0 = p1;
-                    p1 = p2;
-                }
-                cnt += __popc((m ^ (m >> 1)) & 0xffu);
-                const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
-                p0 = __builtin_amdgcn_ldexp(p0, ex);
-                p1 = __builtin_amdgcn_ldexp(p1, ex);
-            };
-            load8(q0, dp);
-            for (int i = 1; i < n; i += 16) {
-                load8(q1, dp + 8);
-                rows8(q0);
-                load8(q0, dp + 16);   // past the end of the last chunk: the next matrix's rows or
-                rows8(q1);            // the couplings, read and not used
-                dp += 16;
-            }
-            // the first point with more than kidx eigenvalues below it bounds lambda above
-            const unsigned long long above = (__ballot((int)cnt > kidx) & gmask) >> lane0;
-            const int f = above ? __builtin_ctzll(above) : S;
-            if (f < S) hi = fma((double)(f + 1), h, lo);
-            if (f > 0) lo = fma((double)f, h, lo);
-        }
-        if (sub != 0) return;
-        lam = 0.5 * (lo + hi);
-        if constexpr (PART == 1) {
-            gs[L.oL + l] = __builtin_amdgcn_ldexp(lam, ex0);
-            return;
-        }
-    } else {
-        lam = __builtin_amdgcn_ldexp(gs[L.oL + l], -ex0);
-    }
-    if constexpr ((PART & 2) != 0) {
-        // the lane's iterate with its reciprocal pivots, row i of every lane side by side
-        const int xs = LDS ? nvl : tk;
-        double2* xp = LDS ? xl + mi * epb + (l - part * epb) : reinterpret_cast<double2*>(gs + L.oY) + l;
-        // inverse iteration (T - lam I) x = b with T - lam I = L D L^T, factored once
-        const double ptol = fmax(2.220446049250313e-16 * tnorm, 1e-300);
-        {
-            double pp = 0.0, ep = 0.0;
-            for (int i0 = 0; i0 < nP; i0 += 8) {
-                double dv[8], ev[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    dv[u] = dm[i0 + u].x - lam;
-                    ev[u] = e[i0 + u];
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int i = i0 + u;
-                    double q = fma(-(ep * ep), pp, dv[u]);
-                    if (fabs(q) < ptol) q = (q < 0.0) ? -ptol : ptol;
-                    pp = sturm_rcp(q);
-                    ep = ev[u];
-                    const double x0 =
-                        (double)(hash_u32((unsigned)(l * 7919 + i * 104729 + 17)) & 0xffffff) / 16777216.0 - 0.5;
-                    xp[i * xs] = make_double2(i < n ? x0 : 0.0, pp);
-                }
-            }
-        }
-        // Per sweep: L y = b upwards (b scaled by sc as it is read), L^T x = D^-1 y downwards
-        // with max |x_i|, then the norm of x / max
-        double sc = 1.0;
-        for (int it = 0; it < 3; ++it) {
-            double2 c0[8], c1[8];
-            double v0[8], v1[8];
-            const auto load8 = [&](double2 (&c)[8], double (&v)[8], int i0) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    c[u] = xp[(i0 + u) * xs];
-                    v[u] = e[i0 + u];
-                }
-            };
-            double y = 0.0, m = 0.0;   // m: minus the multiplier of the next row
-            const auto up8 = [&](const double2 (&c)[8], const double (&v)[8], int i0) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    y = fma(m, y, c[u].x * sc);
-                    m = -(v[u] * c[u].y);
-                    xp[(i0 + u) * xs].x = y;
-                }
-            };
-            load8(c0, v0, 0);
-            for (int i0 = 0; i0 < nP; i0 += 16) {
-                load8(c1, v1, i0 + 8);
-                up8(c0, v0, i0);
-                if (i0 + 16 < nP) load8(c0, v0, i0 + 16);
-                up8(c1, v1, i0 + 8);
-            }
-            double xd = 0.0, mx = 0.0;
-            const auto down8 = [&](const double2 (&c)[8], const double (&v)[8], int i0) {
-#pragma unroll
-                for (int u = 7; u >= 0; --u) {
-                    xd = fma(-(v[u] * c[u].y), xd, c[u].x * c[u].y);
-                    mx = fmax(mx, fabs(xd));
-                    xp[(i0 + u) * xs].x = xd;
-                }
-            };
-            load8(c0, v0, nP - 8);
-            for (int i0 = nP - 8; i0 > 0; i0 -= 16) {
-                load8(c1, v1, i0 - 8);
-                down8(c0, v0, i0);
-                if (i0 - 16 > 0) load8(c0, v0, i0 - 16);
-                down8(c1, v1, i0 - 8);
-            }
-            const double si = mx > 0.0 ? 1.0 / mx : 1.0;
-            double n0 = 0.0, n1 = 0.0;
-            for (int i0 = 0; i0 < nP; i0 += 16) {
-                double t[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) t[u] = xp[(i0 + u) * xs].x;
-#pragma unroll
-                for (int u = 0; u < 16; u += 2) {
-                    const double t0 = t[u] * si, t1 = t[u + 1] * si;
-                    n0 = fma(t0, t0, n0);
-                    n1 = fma(t1, t1, n1);
-                }
-            }
-            const double nrm = n0 + n1;
-            sc = nrm > 0.0 ? si / sqrt(nrm) : si;
-        }
-        // the unit vector out, and the eigenvalue from its Rayleigh quotient
-        double* xo = gs + L.oX + (long long)l * L.ldx;
-        double xq = 0.0, ep = 0.0, rq = 0.0;
-        for (int i0 = 0; i0 < nP; i0 += 8) {
-            double t[8], dv[8], ev[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                t[u] = xp[(i0 + u) * xs].x * sc;
-                dv[u] = dm[i0 + u].x;
-                ev[u] = e[i0 + u];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                rq += t[u] * fma(dv[u], t[u], 2.0 * ep * xq);
-                xq = t[u];
-                ep = ev[u];
-                if (i0 + u < n) xo[i0 + u] = t[u];
-            }
-        }
-        gs[L.oL + l] = __builtin_amdgcn_ldexp(fabs(rq - lam) <= 1e-8 * tnorm ? rq : lam, ex0);
     }
 }
 
@@ -1617,153 +1374,6 @@ __global__ __launch_bounds__(NT) void k_eig_refine(EigArgs a) {
     }
 }
 
-// The same refinement with the blocks in registers and the products on the matrix cores,
-// for mp, np <= 64 RPL and tk <= NW SL: Y = M V_t, thin QR with explicit Q (thinq.h, one
-// barrier per reflector), W = M^T Q, thin QR again, M V'.  It is bound by the chain of
-// 4 tk reflector steps; the blocks pass between the phases through the scratch (L2).  Order
-// 216, tk = 36, 48 matrices: 4.3 ms with the blocks in memory and two barriers per reflector
-// and pass (k_eig_refine), 0.24 ms so.
-// Columns are scaled by a power of two as they are loaded, which changes no subspace and
-// keeps their squared norms in range.
-//
-// Y[x][k] = sum over y of M entries: FIRST: x = ar, y = c (M V), else x = c, y = ar (M^T Q).
-// B element (y, k) at B + k ldb + y; the result goes to out + x out_x + k out_k.  Wave w takes
-// the row tiles w, w + NW, ... and all column tiles; the y loop runs over (dd, t) when
-// FIRST, so that consecutive y stay in one column block of Z.
-template <int NW, int NC, bool FIRST>
-__device__ __forceinline__ void refine_product(const double* Z, int ldz, int tin, int p, int nx, int ny, int tk,
-                                               const double* B, int ldb, double* out, long long out_x,
-                                               long long out_k) {
-    typedef double d4 __attribute__((ext_vector_type(4)));
-    constexpr int UN = 6;   // MFMA steps whose loads are in flight together
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, gq = lane >> 4;
-    const int ts = FIRST ? (tin + 3) / 4 : (ny + 3) / 4, steps = FIRST ? p * ts : ts;
-    for (int x0 = 16 * w; x0 < nx; x0 += 16 * NW) {
-        const int x = x0 + li;
-        const bool xok = x < nx;
-        const int xb = !xok ? 0 : (FIRST ? x * p : (x % tin) * ldz + x / tin);
-        d4 acc[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) acc[c] = d4{0.0, 0.0, 0.0, 0.0};
-        int dd = 0, t4 = 0;
-        for (int s0 = 0; s0 < steps; s0 += UN) {
-            double av[UN], bv[UN][NC];
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const int t = t4 + gq;
-                const bool ok = s0 + u < steps && t < (FIRST ? tin : ny);
-                const int y = FIRST ? dd * tin + t : t;
-                av[u] = ld_or0(ok && xok, Z, (long long)xb + (FIRST ? t * ldz + dd : t * p));
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    const int k = 16 * c + li;
-                    bv[u][c] = ld_or0(ok && k < tk, B, (long long)k * ldb + y);
-                }
-                t4 += 4;
-                if (FIRST && t4 >= 4 * ts) {
-                    t4 = 0;
-                    ++dd;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < UN; ++u)
-#pragma unroll
-                for (int c = 0; c < NC; ++c)
-                    acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u][c], acc[c], 0, 0, 0);
-        }
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int xr = x0 + gq + 4 * r, k = 16 * c + li;
-                if (xr < nx && k < tk) out[xr * out_x + k * out_k] = acc[c][r];
-            }
-    }
-}
-
-// orthonormal basis of the m x tk block X (column-major) in place
-template <int NW, int SL, int RPL>
-__device__ __forceinline__ void refine_orth(double* X, int m, int tk, double (*vbuf)[64 * RPL], double* tau) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    double a[SL][RPL];
-#pragma unroll
-    for (int s = 0; s < SL; ++s) {
-        const int j = s * NW + w;
-        double mx = 0.0;
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const int i = lane + 64 * r;
-            a[s][r] = (j < tk && i < m) ? X[(long long)j * m + i] : 0.0;
-            mx = fmax(mx, fabs(a[s][r]));
-        }
-        for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-        const int ex = mx > 0.0 ? -__builtin_amdgcn_frexp_exp(mx) : 0;
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) a[s][r] = __builtin_amdgcn_ldexp(a[s][r], ex);
-    }
-    thinq_factor<NW, SL, RPL>(a, m, tk, vbuf, tau);
-    __syncthreads();
-    thinq_form<NW, SL, RPL>(a, m, tk, vbuf, tau);
-#pragma unroll
-    for (int s = 0; s < SL; ++s) {
-        const int j = s * NW + w;
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const int i = lane + 64 * r;
-            if (j < tk && i < m) X[(long long)j * m + i] = a[s][r];
-        }
-    }
-}
-
-template <int NW, int SL, int RPL>
-__global__ __launch_bounds__(NW * 64) void k_eig_refine_reg(EigArgs a) {
-    constexpr int NC = (NW * SL + 15) / 16;
-    __shared__ double vbuf[2][64 * RPL];
-    __shared__ double tau[NW * SL];
-    const EigLayout L = eig_layout(a.mz, a.tin, a.p, a.Dc);
-    const int b = blockIdx.x;
-    const int mp = L.mp, np = L.np, tk = L.tk;
-    double* gs = a.scratch + (long long)b * a.ss;
-    const double l0 = gs[L.oL], lt = gs[L.oL + (tk > 0 ? tk - 1 : 0)];
-    // as k_eig_refine, and orders above 224 always: there the step is cheap beside the
-    // tridiagonalisation, and the Gram route alone (order 512, flat spectra, 24 x 24 lattice)
-    // left ln|W| 6e-5 from the oracle, ten times the oracle's own rounding noise
-    if (tk <= 0 || !(l0 > 0.0) || (lt >= 1e-6 * l0 && L.ns <= 224)) return;
-    const double* Z = gs + L.oZ;
-    double* U = a.newU + (long long)b * a.us;
-    double* Go = a.Gout + (long long)b * a.gos;
-    double *Y = gs + L.oY, *W = gs + L.oV;   // mp x tk and np x tk, column-major
-    refine_product<NW, NC, true>(Z, L.ldz, a.tin, a.p, mp, np, tk, U, np, Y, 1, mp);
-    __syncthreads();
-    refine_orth<NW, SL, RPL>(Y, mp, tk, vbuf, tau);
-    __syncthreads();
-    refine_product<NW, NC, false>(Z, L.ldz, a.tin, a.p, np, mp, tk, Y, mp, W, 1, np);
-    __syncthreads();
-    refine_orth<NW, SL, RPL>(W, np, tk, vbuf, tau);
-    __syncthreads();
-    // outputs: V'^T (the rows of the new tensor are the columns of W) and M V'
-    copy_strided(U, W, (long long)tk * np, threadIdx.x, NW * 64);
-    refine_product<NW, NC, true>(Z, L.ldz, a.tin, a.p, mp, np, tk, W, np, Go, tk, 1);
-}
-
-// the smallest register blocking of k_eig_refine_reg that holds the blocks; false when none does
-static bool launch_refine_reg(const EigArgs& a, const EigLayout& L, hipStream_t st) {
-    const int m = L.mp > L.np ? L.mp : L.np, t = L.tk;
-#define RF(NW_, SL_, RPL_)                                                                               \
-    if (m <= 64 * RPL_ && t <= NW_ * SL_) {                                                              \
-        hipLaunchKernelGGL((k_eig_refine_reg<NW_, SL_, RPL_>), dim3(a.batch), dim3(64 * NW_), 0, st, a); \
-        return true;                                                                                     \
-    }
-    RF(4, 4, 1)
-    RF(4, 4, 2)
-    RF(8, 4, 2)
-    RF(8, 5, 4)
-    RF(16, 2, 8)
-    RF(16, 4, 8)
-#undef RF
-    return false;
-}
-
 // k_eig_fin with register-resident vectors (16-lane groups) when ns and tk fit one of the
 // blockings; false when none does
 template <int RPT, int CPG>
@@ -1788,78 +1398,6 @@ static bool launch_fin_reg(const EigArgs& a, const EigLayout& L, size_t bf, size
            fin_try<16, 4>(a, rpt, cpg, bf, cap, st);
 }
 
-// Launch k_eig_tri.  A row of the Sturm count is bound by issue, not by latency, so one wave
-// per SIMD saturates the chip and more points per eigenvalue (work S, steps 52 / log2(S + 1))
-// only pay while waves are missing: S doubles while the lanes fit 1.5 waves per SIMD.  Wide
-// matrices are cut into blocks of 256 lanes so that they spread over the CUs, narrow ones
-// packed until a wave is full.  The iterates are in LDS where one block of them fits (16 bytes
-// per row and lane; else in the scratch).  One launch does both parts where every block
-// stays resident with its iterates; a fuller chip takes two, so that the counts, which need
-// little LDS, keep all SIMDs busy.
-static hipError_t launch_eig_tri(const EigArgs& a, const EigLayout& L, size_t cap, hipStream_t st) {
-    const int tk = L.tk > 0 ? L.tk : 1, n = L.ns, batch = a.batch;
-    struct Shape {
-        int S, mpb, epb, bpm, threads;
-        long long blocks;
-        size_t base, vec;
-    };
-    const auto shape = [&](int S) {
-        Shape t{};
-        t.S = S;
-        if (tk * S >= 256) {
-            t.mpb = 1;
-            t.epb = 256 / S;
-            t.bpm = (tk + t.epb - 1) / t.epb;
-        } else {
-            t.epb = tk;
-            t.bpm = 1;
-            t.mpb = 64 / (tk * S) > 0 ? 64 / (tk * S) : 1;
-            if (t.mpb > batch) t.mpb = batch;
-        }
-        t.threads = (t.mpb * t.epb * S + 63) / 64 * 64;
-        t.blocks = (long long)((batch + t.mpb - 1) / t.mpb) * t.bpm;
-        t.base = (size_t)t.mpb * (2 * (tri_pad(n) + 17) + tri_pad(n) + 16 + 4) * sizeof(double) + 256;
-        t.vec = (size_t)t.mpb * t.epb * tri_pad(n) * 2 * sizeof(double);
-        return t;
-    };
-    int S = 1;
-    while (S < 32 && (long long)batch * tk * S * 2 <= 98304) S *= 2;
-    const Shape v = shape(S);
-#define TRI(PART_, LDS_, sh, bytes_)                                                                              \
-    hipLaunchKernelGGL((k_eig_tri<PART_, LDS_>), dim3((unsigned)sh.blocks), dim3(sh.threads), (bytes_), st, a, \
-                       sh.S, sh.mpb, sh.epb, sh.bpm)
-    const size_t both = v.base + v.vec;
-    if (both <= cap && (v.blocks + 255) / 256 <= (long long)(cap / both)) {
-        TRI(3, true, v, both);
-        return hipGetLastError();
-    }
-    TRI(1, true, v, v.base);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    Shape w = shape(1);
-    while (w.mpb > 1 && w.base + w.vec > cap) {   // fewer matrices, then fewer lanes of one
-        const int half = w.mpb / 2;
-        w.base = (w.base - 256) / w.mpb * half + 256;
-        w.vec = w.vec / w.mpb * half;
-        w.mpb = half;
-        w.threads = (w.mpb * w.epb + 63) / 64 * 64;
-        w.blocks = (batch + w.mpb - 1) / w.mpb;
-    }
-    if (w.base + w.vec > cap) {
-        while (w.epb > 16 && w.base + w.vec > cap) {
-            w.epb = (w.epb + 1) / 2;
-            w.vec = (size_t)w.epb * tri_pad(n) * 2 * sizeof(double);
-        }
-        w.bpm = (tk + w.epb - 1) / w.epb;
-        w.threads = (w.epb + 63) / 64 * 64;
-        w.blocks = (long long)batch * w.bpm;
-    }
-    if (w.base + w.vec <= cap) TRI(2, true, w, w.base + w.vec);
-    else TRI(2, false, w, w.base);
-#undef TRI
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 size_t eig_scratch_doubles(int mz, int tin, int p, int Dc) {
     return (size_t)eig_layout(mz, tin, p, Dc).total;
@@ -1868,7 +1406,7 @@ size_t eig_scratch_doubles(int mz, int tin, int p, int Dc) {
 hipError_t launch_eig(const double* V, long long vs, const double* tau, long long ts, const double* G,
                       long long gs, int mz, int r, int tin, int p, int Dc, double* newU, long long us,
                       double* Gout, long long gos, double* scratch, long long ss, int batch,
-                      hipStream_t st, const double* wyT, long long wys, bool f32_mode) {
+                      hipStream_t st, const double* wyT, long long wys) {
     if (batch <= 0) return hipSuccess;
     EigArgs a;
     a.V = V; a.vs = vs; a.tau = tau; a.ts = ts; a.G = G; a.gs = gs;
@@ -1941,23 +1479,18 @@ hipError_t launch_eig(const double* V, long long vs, const double* tau, long lon
     if (e != hipSuccess) return e;
     if (L.tk > NT) return hipErrorInvalidValue;   // one lane per kept value, at most NT per matrix
     const int tkk = L.tk > 0 ? L.tk : 1;
-    if (f32_mode) {
-        // multisection sub-lanes: two points per eigenvalue and step (measured against one, four
-        // and eight: the bisection is issue-bound, and fewer points cost fewer Sturm sweeps in
-        // all while keeping the chain of steps short)
-        const int S = 2 * tkk <= 64 ? 2 : 1;
-        const int lpm = tkk * S;
-        const int mpb = 64 / lpm > 0 ? 64 / lpm : 1;
-        size_t tri_bytes = (size_t)3 * mpb * L.ns * sizeof(double);
-        const size_t lane_bytes = (size_t)mpb * tkk * L.ns * sizeof(double);   // the iterates
-        const int in_lds = tri_bytes + lane_bytes <= cap ? 1 : 0;
-        if (in_lds) tri_bytes += lane_bytes;
-        hipLaunchKernelGGL(k_eig_tri_piv, dim3((unsigned)((batch + mpb - 1) / mpb)), dim3(mpb * lpm), tri_bytes, st,
-                           a, S, mpb, in_lds);
-    } else {
-        e = launch_eig_tri(a, L, cap, st);
-        if (e != hipSuccess) return e;
-    }
+    // multisection sub-lanes: two points per eigenvalue and step (measured against one, four
+    // and eight: the bisection is issue-bound, and fewer points cost fewer Sturm sweeps in
+    // all while keeping the chain of steps short)
+    const int S = 2 * tkk <= 64 ? 2 : 1;
+    const int lpm = tkk * S;
+    const int mpb = 64 / lpm > 0 ? 64 / lpm : 1;
+    size_t tri_bytes = (size_t)3 * mpb * L.ns * sizeof(double);
+    const size_t lane_bytes = (size_t)mpb * tkk * L.ns * sizeof(double);   // the iterates
+    const int in_lds = tri_bytes + lane_bytes <= cap ? 1 : 0;
+    if (in_lds) tri_bytes += lane_bytes;
+    hipLaunchKernelGGL(k_eig_tri, dim3((unsigned)((batch + mpb - 1) / mpb)), dim3(mpb * lpm), tri_bytes, st,
+                       a, S, mpb, in_lds);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (!launch_fin_reg(a, L, bf, cap, st)) {
@@ -1967,7 +1500,6 @@ hipError_t launch_eig(const double* V, long long vs, const double* tau, long lon
     e = hipGetLastError();
     if (e != hipSuccess) return e;
 
-    if (!f32_mode && launch_refine_reg(a, L, st)) return hipGetLastError();
     const size_t br = (size_t)(L.mp + L.np) * L.tk * sizeof(double);
     if (br <= cap / 2) hipLaunchKernelGGL(k_eig_refine<true>, dim3(batch), dim3(NT), br, st, a);
     else hipLaunchKernelGGL(k_eig_refine<false>, dim3(batch), dim3(NT), 0, st, a);

@@ -51,15 +51,27 @@ struct EigArgs {
 };
 size_t eig_scratch_doubles(int mz, int tin, int p, int Dc);
 // wyT != nullptr: the reflectors came from the blocked QR, whose WY blocks (wyT, stride wys
-// per matrix) apply Q to [G; 0] on the matrix cores.
-// f32_mode: the call of a float32 or bfloat16 mode, whose next product rounds the factors to
-// float32: there a different rounding of this step, harmless in float64, moves ln|W| by up to
-// 5e-8 relative (measured, 8x8 D = 4), so those modes keep their kernels' bits (pivot Sturm
-// counts, LDS refinement)
+// per matrix) apply Q to [G; 0] on the matrix cores
 hipError_t launch_eig(const double* V, long long vs, const double* tau, long long ts, const double* G,
                       long long gs, int mz, int r, int tin, int p, int Dc, double* newU, long long us,
                       double* Gout, long long gos, double* scratch, long long ss, int batch,
-                      hipStream_t st, const double* wyT = nullptr, long long wys = 0, bool f32_mode = false);
+                      hipStream_t st, const double* wyT = nullptr, long long wys = 0);
+
+// Truncation of one centre in float64 (k_trunc.hip): the centre M (mp x np, row-major) is in the
+// first mp np doubles of the matrix's scratch (trunc_scratch_doubles, stride ss); newU (tk x np
+// row-major, tk = min(Dc, mp, np)) and H = F newU^T (nf x tk row-major) from F (nf x np row-major).
+// trunc_fits: orders min(mp, np) <= 512, sides <= 512, tk <= 64.
+struct TruncArgs {
+    int mp, np, Dc, nf;
+    double* newU; long long us;
+    const double* F; long long fs;
+    double* H; long long hs;
+    double* scratch; long long ss;
+    int batch;
+};
+bool trunc_fits(int mp, int np, int Dc);
+size_t trunc_scratch_doubles(int mp, int np, int Dc);
+hipError_t launch_trunc(const TruncArgs& a, hipStream_t st);
 
 // blocked Householder QR (k_qrb.hip) for matrices beyond the register kernels: panels of
 // qrb_panel_width(m) columns factorised in registers, trailing updates in compact WY form

@@ -163,8 +163,28 @@ public:
         sweeps = c->vc_sweeps;
         vcU.assign(Ly, 0);
         vcL.assign(Ly, 0);
-        for (int i = 0; i + 1 < Ly; ++i) vcU[i] = use_vc(tU[i]);
-        for (int i = Ly - 1; i >= 1; --i) vcL[i] = use_vc(tL[i]);
+        trU.assign(Ly, 0);
+        trL.assign(Ly, 0);
+        for (int i = 0; i + 1 < Ly; ++i) {
+            vcU[i] = use_vc(tU[i]);
+            trU[i] = !vcU[i] && use_tr(tU[i]);
+        }
+        for (int i = Ly - 1; i >= 1; --i) {
+            vcL[i] = use_vc(tL[i]);
+            trL[i] = !vcL[i] && use_tr(tL[i]);
+        }
+    }
+
+    // The float64 truncation kernels (trunc_step_f64) where every centre of the row fits them;
+    // larger bonds take trunc_step, and so do the float32 and bfloat16 modes: their next
+    // product rounds the factors to float32, which turns any other rounding of a
+    // factorisation, harmless in float64, into changes of up to 5e-8 of ln|W| (8x8, D = 4), so
+    // they keep their kernels' bits.
+    bool use_tr(const Trunc& t) const {
+        if (ar != Arith::F64) return false;
+        for (int j = 1; j < Lx; ++j)
+            if (!trunc_fits(t.rho[j], t.p * t.tau[j + 1], Dc)) return false;
+        return true;
     }
 
     // Variational compression replaces the SVD truncation of a boundary wherever the
@@ -265,10 +285,58 @@ public:
             }
         };
         for (int i = 0; i + 1 < Ly; ++i)
-            if (!vcU[i]) visit(tU[i]);
+            if (!vcU[i] && !trU[i]) visit(tU[i]);
         if (need_L)
             for (int i = Ly - 1; i >= 1; --i)
-                if (!vcL[i]) visit(tL[i]);
+                if (!vcL[i] && !trL[i]) visit(tL[i]);
+        // the float64 truncation: one column tensor and its QR scratch, R of every cut, the raw
+        // products with the kept right part, that part twice, and the centre's scratch
+        {
+            s_Rc.assign(Lx + 1, 0);
+            s_Xc = s_tauc = s_wyc = s_S1 = s_Fc = s_Hc = s_tr = 0;
+            bool any = false;
+            auto visit_tr = [&](const Trunc& t) {
+                any = true;
+                for (int j = 0; j < Lx; ++j) {
+                    const long long rows = (long long)t.rho[j] * t.p, cols = t.K[j + 1];
+                    const long long tin = t.tau[j + 1];
+                    if (j + 1 < Lx) {
+                        s_Xc = std::max(s_Xc, rows * cols);
+                        s_tauc = std::max(s_tauc, std::min(rows, cols));
+                        s_Rc[j + 1] = std::max(s_Rc[j + 1], (long long)t.rho[j + 1] * cols);
+                        s_Y = std::max(s_Y, (long long)t.rho[j] * Dh[j] * t.pin * t.chi[j + 1]);
+                        if (use_qrb((int)rows, (int)cols)) {
+                            s_wyc = std::max(s_wyc, qrb_wy_doubles((int)rows, (int)cols));
+                            s_vc = std::max(s_vc, qrb_vc_doubles((int)rows));
+                            s_wq = std::max(s_wq, qrb_wq_doubles((int)cols));
+                        }
+                    }
+                    s_S1 = std::max(s_S1, (long long)t.chi[j] * t.pin * Dh[j + 1] * tin);
+                    s_Fc = std::max(s_Fc, (long long)t.K[j] * t.p * tin);
+                    if (j > 0) {
+                        s_Hc = std::max(s_Hc, (long long)t.K[j] * t.tau[j]);
+                        s_tr = std::max<long long>(s_tr, trunc_scratch_doubles(t.rho[j], t.p * (int)tin, Dc));
+                    }
+                }
+            };
+            for (int i = 0; i + 1 < Ly; ++i)
+                if (trU[i]) visit_tr(tU[i]);
+            if (need_L)
+                for (int i = Ly - 1; i >= 1; --i)
+                    if (trL[i]) visit_tr(tL[i]);
+            o_Rc.assign(Lx + 1, 0);
+            if (any) {
+                o_Xc = L.alloc(s_Xc);
+                o_tauc = L.alloc(s_tauc);
+                o_wyc = s_wyc > 0 ? L.alloc(s_wyc) : 0;
+                for (int c = 1; c < Lx; ++c) o_Rc[c] = L.alloc(s_Rc[c]);
+                o_S1 = L.alloc(s_S1);
+                o_Fc = L.alloc(s_Fc);
+                o_Hc[0] = L.alloc(s_Hc);
+                o_Hc[1] = L.alloc(s_Hc);
+                o_tr = L.alloc(s_tr);
+            }
+        }
         // variational compression: overlap environments L_c and R_c per cut c ([c][a][l],
         // bond x bond x horizontal leg), two contraction temporaries, the updated site
         // tensor and the triangular factor of the guess's canonicalisation
@@ -324,10 +392,10 @@ public:
             }
         };
         for (int i = 0; i + 1 < Ly; ++i)
-            if (!vcU[i]) visit_eig(tU[i]);
+            if (!vcU[i] && !trU[i]) visit_eig(tU[i]);
         if (need_L)
             for (int i = Ly - 1; i >= 1; --i)
-                if (!vcL[i]) visit_eig(tL[i]);
+                if (!vcL[i] && !trL[i]) visit_eig(tL[i]);
         o_eig = L.alloc(s_eig);
         // single-row partials
         s_P.assign(Lx + 1, 1);
@@ -597,8 +665,7 @@ public:
             const int mz = t.rho[j] * p;
             KL(timed(PEPS_KC_SVD, Bcur * svd_flops(mz, 0, 1, p, t.tau[j]), [&] {
                 return launch_eig(nullptr, 0, buf(o_tau[0]), 0, buf(o_X[j]), s_X[j], mz, mz, 1, p, Dc,
-                                  Eout.p, Eout.bs, buf(o_G[0]), s_G, buf(o_eig), s_eig, Bcur, st_, nullptr, 0,
-                                  ar != Arith::F64);
+                                  Eout.p, Eout.bs, buf(o_G[0]), s_G, buf(o_eig), s_eig, Bcur, st_);
             }));
         }
         for (int j = Lx - 2; j >= 1; --j) {
@@ -608,8 +675,7 @@ public:
                 const bool blocked = use_qrb(mz, t.K[j + 1]);
                 return launch_eig(buf(o_X[j]), s_X[j], buf(o_tau[j]), s_tau[j], buf(o_G[cur]), s_G, mz,
                                   t.rho[j + 1], t.tau[j + 1], p, Dc, Eout.p, Eout.bs, buf(o_G[cur ^ 1]), s_G,
-                                  buf(o_eig), s_eig, Bcur, st_, blocked ? buf(o_wy[j]) : nullptr, s_wy[j],
-                                  ar != Arith::F64);
+                                  buf(o_eig), s_eig, Bcur, st_, blocked ? buf(o_wy[j]) : nullptr, s_wy[j]);
             }));
             cur ^= 1;
         }
@@ -621,6 +687,80 @@ public:
                               t.rho[1], t.tau[1], Eout.p, Eout.bs, lin.p, lout.p, buf(o_svd), s_svd,
                               Bcur, st_));
         }
+        return hipSuccess;
+    }
+
+    // The same truncation in float64 without Q factors (k_trunc.hip): the QR sweep keeps only R
+    // of every cut; from the right, F_j = (raw site j) H_{j+1} with H_{j+1} the raw right part
+    // contracted with the kept basis, the centre is R_j F_j, its leading right singular
+    // vectors are the new tensor V_j and H_j = F_j V_j.
+    hipError_t trunc_step_f64(bool down, int row) {
+        const Trunc& t = down ? tU[row] : tL[row];
+        const long long s_in = down ? D2 : 1, s_out = down ? 1 : D2;
+        const int pin = t.pin, p = t.p;
+        const Arith F64 = Arith::F64;
+        auto Ein = [&](int j) { return down ? envU(row, j) : envL(row, j); };
+        auto Eout = [&](int j) { return down ? envU(row + 1, j) : envL(row - 1, j); };
+        auto Rcut = [&](int c) { return c == 0 ? ones() : op(o_Rc[c], s_Rc[c]); };
+        for (int j = 0; j + 1 < Lx; ++j) {
+            const int chj = t.chi[j], chj1 = t.chi[j + 1], Dl = Dh[j], Dr = Dh[j + 1];
+            const int rho = t.rho[j], cols = t.K[j + 1];
+            const long long rows = (long long)rho * p;
+            const Op Y = op(o_Y, s_Y), X = op(o_Xc, s_Xc), R = Rcut(j + 1);
+            // Y[(a',l),(u,b)] = sum_a R[a', a*Dl+l] E[a,(u,b)]
+            CK(gemm_a(F64, rho * Dl, pin * chj1, chj, Rcut(j), I2(Dl, t.K[j], 1), I1(Dl), Gather{}, Ein(j),
+                      I1((long long)pin * chj1), I1(1), Gather{}, Y, I1((long long)pin * chj1), I1(1)));
+            // X[(a',d),(b,r)] (column-major) = sum_{l,u} Y[a',l,u,b] T[l,u,r,d]
+            CK(gemm_a(F64, rho * chj1, Dr * p, Dl * pin, Y, I2(chj1, (long long)Dl * pin * chj1, 1),
+                      I2(pin, (long long)pin * chj1, chj1), Gather{}, site_op(row, j), I2(pin, D3, s_in),
+                      I2(p, D, s_out), site_gather(row, j, 0), X, I2(chj1, p, Dr * rows), I2(p, rows, 1)));
+            const bool blocked = use_qrb((int)rows, cols);
+            if (rows * cols > s_Xc || std::min<long long>(rows, cols) > s_tauc ||
+                !bounds_ok("qr R", R, (long long)t.rho[j + 1] * cols - 1, 0) ||
+                (blocked && (qrb_wy_doubles((int)rows, cols) > s_wyc || qrb_vc_doubles((int)rows) > s_vc ||
+                             qrb_wq_doubles(cols) > s_wq))) {
+                if (bounds_msg.empty()) bounds_msg = "internal bounds check failed in qr";
+                return hipErrorInvalidValue;
+            }
+            KL(timed(PEPS_KC_QR, Bcur * qr_flops((double)rows, cols), [&] {
+                if (blocked)
+                    return launch_qr_blocked(X.p, X.bs, (int)rows, cols, R.p, R.bs, buf(o_tauc), s_tauc, buf(o_wyc),
+                                             s_wyc, buf(o_vc), s_vc, buf(o_wq), s_wq, Bcur, st_);
+                return launch_qr(X.p, X.bs, (int)rows, cols, R.p, R.bs, buf(o_tauc), s_tauc, Bcur, st_);
+            }));
+        }
+        int cur = 0;
+        for (int j = Lx - 1; j >= 0; --j) {
+            const int chj = t.chi[j], chj1 = t.chi[j + 1], Dl = Dh[j], Dr = Dh[j + 1];
+            const int tin = t.tau[j + 1], np = p * tin, rho = t.rho[j], K = t.K[j];
+            const Op H = j + 1 == Lx ? ones() : op(o_Hc[cur], s_Hc), S1 = op(o_S1, s_S1);
+            const Op F = j == 0 ? Eout(0) : op(o_Fc, s_Fc);
+            // S1[(a,u),(r,t)] = sum_b E[a,u,b] H[(b,r),t]
+            CK(gemm_a(F64, chj * pin, Dr * tin, chj1, Ein(j), I1(chj1), I1(1), Gather{}, H, I1(Dr * tin), I1(1),
+                      Gather{}, S1, I1(Dr * tin), I1(1)));
+            // F[(a,l),(d,t)] = sum_{u,r} S1[a,u,r,t] T[l,u,r,d]
+            CK(gemm_a(F64, chj * tin, Dl * p, pin * Dr, S1, I2(tin, (long long)pin * Dr * tin, 1),
+                      I2(Dr, (long long)Dr * tin, tin), Gather{}, site_op(row, j), I2(Dr, s_in, D),
+                      I2(p, D3, s_out), site_gather(row, j, 0), F, I2(tin, (long long)Dl * np, 1), I2(p, np, tin)));
+            if (j == 0) break;
+            const Op M = op(o_tr, s_tr), Hn = op(o_Hc[cur ^ 1], s_Hc), En = Eout(j);
+            CK(gemm_a(F64, rho, np, K, Rcut(j), I1(K), I1(1), Gather{}, F, I1(np), I1(1), Gather{}, M, I1(np), I1(1)));
+            if ((long long)trunc_scratch_doubles(rho, np, Dc) > s_tr || !trunc_fits(rho, np, Dc) ||
+                !bounds_ok("truncation V", En, (long long)t.tau[j] * np - 1, 0) ||
+                !bounds_ok("truncation H", Hn, (long long)K * t.tau[j] - 1, 0) ||
+                t.tau[j] != std::min(Dc, std::min(rho, np))) {
+                if (bounds_msg.empty()) bounds_msg = "internal bounds check failed in the truncation";
+                return hipErrorInvalidValue;
+            }
+            TruncArgs a{rho, np, Dc, K, En.p, En.bs, F.p, F.bs, Hn.p, Hn.bs, M.p, s_tr, Bcur};
+            KL(timed(PEPS_KC_SVD, Bcur * svd_flops((double)rho * p, j + 1 < Lx ? t.rho[j + 1] : 0, tin, p, t.tau[j]),
+                     [&] { return launch_trunc(a, st_); }));
+            cur ^= 1;
+        }
+        const Op E0 = Eout(0), lin = down ? logU(row) : logL(row), lout = down ? logU(row + 1) : logL(row - 1);
+        const int n0 = p * t.tau[1];
+        if (!bounds_ok("truncation norm", E0, n0 - 1, 0)) return hipErrorInvalidValue;
+        KL(launch_vc_norm(E0.p, E0.bs, n0, lin.p, lout.p, Bcur, st_));
         return hipSuccess;
     }
 
@@ -994,11 +1134,15 @@ public:
         KL(launch_fill(buf(o_zero), Bn, 0.0, st));
         if (fuse_pairs) KL(launch_site_tables(Ad, reinterpret_cast<float*>(buf(o_site32)), Lx, Ly, D, st));
         KL(launch_fill(buf(o_logU[0]), Bn, 0.0, st));
-        for (int i = 0; i + 1 < Ly; ++i) CK(vcU[i] ? vc_step(true, i) : trunc_step(true, i));
+        auto boundary = [&](bool down, int i) {
+            if (down ? vcU[i] : vcL[i]) return vc_step(down, i);
+            return (down ? trU[i] : trL[i]) ? trunc_step_f64(down, i) : trunc_step(down, i);
+        };
+        for (int i = 0; i + 1 < Ly; ++i) CK(boundary(true, i));
         const bool need_L = want_eloc || want_grad;
         if (need_L) {
             KL(launch_fill(buf(o_logL[Ly - 1]), Bn, 0.0, st));
-            for (int i = Ly - 1; i >= 1; --i) CK(vcL[i] ? vc_step(false, i) : trunc_step(false, i));
+            for (int i = Ly - 1; i >= 1; --i) CK(boundary(false, i));
         }
         if (want_grad) KL(launch_fill(buf(o_delta), (long long)Bn * N * D4, 0.0, st));
         const int nH = Ly * (Lx - 1), nV = (Ly - 1) * Lx, nD = (Ly - 1) * (Lx - 1);
@@ -1170,6 +1314,11 @@ public:
     bool fuse_pairs = false;
     int sweeps = 0;                         // variational compression sweeps (0: SVD truncation)
     std::vector<char> vcU, vcL;             // which truncations are variational
+    std::vector<char> trU, trL;             // which run in trunc_step_f64
+    std::vector<long long> s_Rc;
+    std::vector<size_t> o_Rc;
+    size_t o_Xc = 0, o_tauc = 0, o_wyc = 0, o_S1 = 0, o_Fc = 0, o_Hc[2] = {0, 0}, o_tr = 0;
+    long long s_Xc = 0, s_tauc = 0, s_wyc = 0, s_S1 = 0, s_Fc = 0, s_Hc = 0, s_tr = 0;
     std::vector<long long> vc_eoff;         // offset of cut c's overlap environment
     size_t o_vL = 0, o_vR = 0, o_vZ1 = 0, o_vZ2 = 0, o_vM = 0, o_vRf = 0, o_vW = 0;
     long long s_vE = 0, s_vZ1 = 0, s_vZ2 = 0, s_vM = 0, s_vRf = 0, s_vW = 0;

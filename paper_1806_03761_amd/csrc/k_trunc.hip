@@ -16,6 +16,7 @@
 //   k_eig_tri         eigenvalues and tridiagonal eigenvectors
 //   k_tr_vec          orthonormalisation, back-transformation, refinement, V^T and H
 #include "common.h"
+#include "householder.h"
 #include "kernels.h"
 #include "thinq.h"
 
@@ -53,36 +54,6 @@ __host__ __device__ inline TruncLayout trunc_layout(int mp, int np, int Dc) {
 // ---------------------------------------------------------------------------
 // tridiagonalisation in registers
 // ---------------------------------------------------------------------------
-// Householder scalars of a column with pivot entry al and squared norm sq below it (dlarfg:
-// beta = -sign(al) norm, tau = (beta - al) / beta, v = x / (al - beta)) from one reciprocal
-// square root and one reciprocal, each the hardware estimate with two Newton steps: half the
-// dependent chain of a square root and two divisions.
-__device__ __forceinline__ void hh_scalars(double al, double sq, double& tk, double& be, double& sc) {
-    const double s2 = fma(al, al, sq);
-    if (sq == 0.0) {
-        tk = 0.0;
-        be = al;
-        sc = 0.0;
-    } else if (s2 > 1e-280 && s2 < 1e280) {
-        double r = __builtin_amdgcn_rsq(s2);
-        r = fma(fma(-s2 * r, r, 1.0), 0.5 * r, r);
-        r = fma(fma(-s2 * r, r, 1.0), 0.5 * r, r);
-        double nrm = s2 * r;
-        nrm = fma(fma(-nrm, nrm, s2), 0.5 * r, nrm);
-        const double den = fabs(al) + nrm;
-        double q = __builtin_amdgcn_rcp(den);
-        q = fma(fma(-den, q, 1.0), q, q);
-        q = fma(fma(-den, q, 1.0), q, q);
-        be = -copysign(nrm, al);
-        sc = copysign(q, al);
-        tk = den * r;
-    } else {
-        be = -copysign(sqrt(s2), al);
-        tk = (be - al) / be;
-        sc = 1.0 / (al - be);
-    }
-}
-
 // A <- H_k A H_k step by step, A (order ns <= GR NR = GC NC, full storage) in the registers of a
 // GR x GC thread grid: thread (ti, tj) holds the rows ti + GR u and columns tj + GC w.  The
 // cyclic layout keeps the work balanced as the trailing matrix shrinks, and the steps whose
@@ -855,7 +826,7 @@ __device__ __forceinline__ void back_transform(const double* Xg, int ldx, const 
                     if (q < j) s = fma(row[q], g[q * 16], s);   // row[q] = 0 for q < lane
                 const double tj = g[j * 16];
                 row[j] = j < lane ? 0.0 : (j == lane ? tj : -tj * s);
-                asm volatile("" ::: "memory");   // one column's LDS reads at a time
+                asm volatile("" : "+v"(row[j])::"memory");   // one column's LDS reads at a time
             }
         }
         __syncthreads();

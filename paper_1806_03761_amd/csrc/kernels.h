@@ -57,6 +57,14 @@ hipError_t launch_eig(const double* V, long long vs, const double* tau, long lon
                       double* Gout, long long gos, double* scratch, long long ss, int batch,
                       hipStream_t st, const double* wyT = nullptr, long long wys = 0);
 
+// R (r x n row-major, zeros below the diagonal, r = min(m, n), scaled by a power of two) of row-major
+// m x n matrices in float64 (k_qrr.hip); X is overwritten.  W: qrr_scratch_doubles(m) doubles per
+// matrix (stride ws).
+bool qrr_fits(int m, int n);
+long long qrr_scratch_doubles(int m);
+hipError_t launch_qr_r(double* X, long long xs, int m, int n, double* R, long long rs, double* W, long long ws,
+                       int batch, hipStream_t st);
+
 // Truncation of one centre in float64 (k_trunc.hip): the centre M (mp x np, row-major) is in the
 // first mp np doubles of the matrix's scratch (trunc_scratch_doubles, stride ss); newU (tk x np
 // row-major, tk = min(Dc, mp, np)) and H = F newU^T (nf x tk row-major) from F (nf x np row-major).

@@ -305,11 +305,7 @@ public:
                         s_tauc = std::max(s_tauc, std::min(rows, cols));
                         s_Rc[j + 1] = std::max(s_Rc[j + 1], (long long)t.rho[j + 1] * cols);
                         s_Y = std::max(s_Y, (long long)t.rho[j] * Dh[j] * t.pin * t.chi[j + 1]);
-                        if (use_qrb((int)rows, (int)cols)) {
-                            s_wyc = std::max(s_wyc, qrb_wy_doubles((int)rows, (int)cols));
-                            s_vc = std::max(s_vc, qrb_vc_doubles((int)rows));
-                            s_wq = std::max(s_wq, qrb_wq_doubles((int)cols));
-                        }
+                        if (use_qrr((int)rows, (int)cols)) s_wyc = std::max(s_wyc, qrr_scratch_doubles((int)rows));
                     }
                     s_S1 = std::max(s_S1, (long long)t.chi[j] * t.pin * Dh[j + 1] * tin);
                     s_Fc = std::max(s_Fc, (long long)t.K[j] * t.p * tin);
@@ -710,22 +706,23 @@ public:
             // Y[(a',l),(u,b)] = sum_a R[a', a*Dl+l] E[a,(u,b)]
             CK(gemm_a(F64, rho * Dl, pin * chj1, chj, Rcut(j), I2(Dl, t.K[j], 1), I1(Dl), Gather{}, Ein(j),
                       I1((long long)pin * chj1), I1(1), Gather{}, Y, I1((long long)pin * chj1), I1(1)));
-            // X[(a',d),(b,r)] (column-major) = sum_{l,u} Y[a',l,u,b] T[l,u,r,d]
+            // X[(a',d),(b,r)] = sum_{l,u} Y[a',l,u,b] T[l,u,r,d], row-major for the blocked R factor,
+            // column-major for the register kernels
+            const bool blocked = use_qrr((int)rows, cols);
             CK(gemm_a(F64, rho * chj1, Dr * p, Dl * pin, Y, I2(chj1, (long long)Dl * pin * chj1, 1),
                       I2(pin, (long long)pin * chj1, chj1), Gather{}, site_op(row, j), I2(pin, D3, s_in),
-                      I2(p, D, s_out), site_gather(row, j, 0), X, I2(chj1, p, Dr * rows), I2(p, rows, 1)));
-            const bool blocked = use_qrb((int)rows, cols);
+                      blocked ? I2(Dr, s_out, D) : I2(p, D, s_out), site_gather(row, j, 0), X,
+                      blocked ? I2(chj1, (long long)p * cols, Dr) : I2(chj1, p, Dr * rows),
+                      blocked ? I2(Dr, cols, 1) : I2(p, rows, 1)));
             if (rows * cols > s_Xc || std::min<long long>(rows, cols) > s_tauc ||
                 !bounds_ok("qr R", R, (long long)t.rho[j + 1] * cols - 1, 0) ||
-                (blocked && (qrb_wy_doubles((int)rows, cols) > s_wyc || qrb_vc_doubles((int)rows) > s_vc ||
-                             qrb_wq_doubles(cols) > s_wq))) {
+                (blocked && qrr_scratch_doubles((int)rows) > s_wyc)) {
                 if (bounds_msg.empty()) bounds_msg = "internal bounds check failed in qr";
                 return hipErrorInvalidValue;
             }
             KL(timed(PEPS_KC_QR, Bcur * qr_flops((double)rows, cols), [&] {
                 if (blocked)
-                    return launch_qr_blocked(X.p, X.bs, (int)rows, cols, R.p, R.bs, buf(o_tauc), s_tauc, buf(o_wyc),
-                                             s_wyc, buf(o_vc), s_vc, buf(o_wq), s_wq, Bcur, st_);
+                    return launch_qr_r(X.p, X.bs, (int)rows, cols, R.p, R.bs, buf(o_wyc), s_wyc, Bcur, st_);
                 return launch_qr(X.p, X.bs, (int)rows, cols, R.p, R.bs, buf(o_tauc), s_tauc, Bcur, st_);
             }));
         }
@@ -1301,6 +1298,8 @@ public:
     long long s_vc = 0, s_wq = 0;
     // the blocked QR (matrix-core WY updates) for matrices beyond the register kernels
     static bool use_qrb(int rows, int cols) { return (rows > 512 || cols > 128) && qrb_fits(rows, cols); }
+    // the blocked R factor of the float64 truncation, for the same sizes
+    static bool use_qrr(int rows, int cols) { return (rows > 512 || cols > 128) && qrr_fits(rows, cols); }
     size_t o_site32 = 0, o_act = 0;
     const int8_t* skip_ = nullptr;
     long long skip_bs_ = 0;

@@ -67,3 +67,19 @@ def test_truncation_independent_of_the_batch(shape, batch):
         l1, s1, f1 = peps.log_amplitude(Ad, Sd[b:b + 1].contiguous(), lat)
         assert int(f1[0]) == int(fl[b]) == 0 and int(s1[0]) == int(sg[b])
         assert float(l1[0]) == float(la[b])
+
+
+# column tensors at the row counts where the blocked R factor changes its blocking (128-row tiles
+# of its eight waves, 16-column panels above 1408 rows, row blocks above 2048) and at column
+# counts that leave a part of a 32- or 16-column panel; more columns than rows in the first row
+@pytest.mark.parametrize("shape", [(8, 5, 5, 21), (8, 5, 5, 25), (8, 5, 6, 33), (8, 5, 6, 36), (6, 5, 7, 43),
+                                   (6, 4, 7, 49), (7, 4, 8, 64), (4, 3, 9, 50), (4, 3, 12, 20), (4, 3, 16, 17),
+                                   (4, 4, 16, 32)])
+def test_blocked_r_factor(shape):
+    Lx, Ly, D, Dc = shape
+    lat = Lattice(Lx, Ly, D, Dc)
+    A, S = make_random(lat, 2, 80 + D)
+    la, sg, fl = (t.cpu().numpy() for t in _peps().log_amplitude(*_dev(A, S), lat, "f64"))
+    la_o, sg_o, fl_o = O.log_amplitude(A, lat, S)
+    assert not fl.any() and not np.any(fl_o) and np.array_equal(sg, sg_o)
+    assert np.all(np.abs(la - la_o) <= 1e-10 * np.maximum(1, np.abs(la_o)))

@@ -500,6 +500,11 @@ hipError_t launch_mgemm(const GemmArgs& g, Arith ar, hipStream_t st, int tile) {
     // product, whose stores then coalesce.  Same products, same ascending k: same bits.
     auto unit = [](const Idx2& x) { return x.s_inner == 1 && x.inner > 1; };
     if (unit(g.cm) && !unit(g.cn)) return launch_mgemm(gemm_transposed(g), ar, st, tile);
+    if (tile <= 0 && ar == Arith::F64) {
+        bool done;
+        const hipError_t e = launch_dgemm(g, st, done);
+        if (done || e != hipSuccess) return e;
+    }
     // the kernels hold the free-index offsets of A and B in 32 bits
     const long long ma = idx_bound(g.am, g.M), nb = idx_bound(g.bn, g.N);
     if (ma < 0 || nb < 0 || ma > 0x7fffffffLL || nb > 0x7fffffffLL) return hipErrorInvalidValue;

@@ -83,3 +83,38 @@ def test_blocked_r_factor(shape):
     la_o, sg_o, fl_o = O.log_amplitude(A, lat, S)
     assert not fl.any() and not np.any(fl_o) and np.array_equal(sg, sg_o)
     assert np.all(np.abs(la - la_o) <= 1e-10 * np.maximum(1, np.abs(la_o)))
+
+
+# the float64 products computed from registers (the untuned choice) against the LDS-staged
+# kernel (tile 4), which sum every output alike: equal bits over odd legs and bonds (a K that 4
+# does not divide, split indices of 2 to 7, ragged edges of every block shape) and both
+# boundary methods
+@pytest.mark.parametrize("case", [(4, 4, 2, 3, 5, 0), (5, 4, 3, 7, 33, 0), (4, 5, 5, 17, 9, 0),
+                                  (4, 3, 7, 19, 2, 0), (4, 5, 3, 9, 300, 2),
+                                  (5, 4, 6, 30, 7, 1), (4, 4, 2, 1, 700, 0)])
+def test_register_products_equal_staged(case, tmp_path):
+    Lx, Ly, D, Dc, batch, sweeps = case
+    p, lat = _peps(), Lattice(Lx, Ly, D, Dc)
+    A, S = make_random(lat, batch, 300 + D)
+    Ad, Sd = _dev(A, S)
+    keys, saved, path = [], str(tmp_path / "saved.txt"), str(tmp_path / "t.txt")
+    p.tune_save(saved)
+    p.set_truncation(sweeps)
+    try:
+        base = [t.cpu().numpy() for t in p.evaluate(Ad, Sd, lat, "f64", grad_mode=3)]
+        p.autotune(Ad, Sd, lat, "f64")
+        p.tune_save(path)
+        keys = [ln.split()[0] for ln in open(path) if ln.strip() and not ln.startswith("#")]
+        with open(path, "w") as f:
+            f.writelines(f"{k} 4\n" for k in keys)
+        p.tune_load(path)
+        got = [t.cpu().numpy() for t in p.evaluate(Ad, Sd, lat, "f64", grad_mode=3)]
+    finally:
+        with open(path, "w") as f:
+            f.writelines(f"{k} 0\n" for k in keys)
+        p.tune_load(path)
+        p.tune_load(saved)
+        p.set_truncation(0)
+    assert keys
+    for x, y in zip(got, base):
+        assert np.array_equal(x, y)

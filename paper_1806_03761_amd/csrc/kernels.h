@@ -122,6 +122,28 @@ hipError_t launch_vc_norm(double* x, long long xs, int n, const double* lin, dou
                           hipStream_t st);
 
 // misc
+// fused single- and two-row sandwich steps in float64 (k_step.hip), both directions.  Legs and
+// bonds by their place in the chain: X[f,b,b',g] (b' in the two-row step only), E1[f,u,f'],
+// site A[b,u,a,m], site B[b',m,a',q], E2[g,q,g'], Y[f',a,a',g']
+struct StepArgs {
+    bool pair;
+    bool q_outer;                        // k order of the last product: (q, g) instead of (g, q)
+    int F, F1, G, G1, H, H1, Du, Dm, Dq; // sizes of f, f', g, g', b = b', a = a', u, m, q
+    const double* X; long long xs; long long xf, xb, xb2, xg;
+    const double* E1; long long e1s; long long e1f, e1u, e1f1;
+    const double* E2; long long e2s; long long e2g, e2q, e2g1;
+    const double* SA; const double* SB;  // spin 0 slices; strides of (b, u), (a, m) and (b', m), (a', q)
+    int sak[2], san[2], sbk[2], sbn[2];
+    const int8_t* selA; const int8_t* selB; long long sel_bs, slice; int flipA, flipB;
+    double* Y; long long ys; long long yf, ya, ya2, yg;
+    const double* lin; double* lout;     // lout != nullptr: max-abs rescale (step64_rescales), log into lout
+    int batch;
+    const int8_t* skip = nullptr;        // sample b skipped when skip[b * skip_bs] == 0
+    long long skip_bs = 0;
+};
+bool step64_fits(const StepArgs& a);
+bool step64_rescales(const StepArgs& a);
+hipError_t launch_step64(const StepArgs& a, hipStream_t st);
 // fused two-row sandwich step (float32, legs <= 4, boundary bonds <= 16; see k_pair.hip)
 struct PairArgs {
     int cu, cu1, cl, cl1, Du, Dm, Dq, h, h1;

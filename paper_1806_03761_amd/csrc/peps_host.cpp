@@ -146,6 +146,7 @@ public:
         // fused single- and two-row sandwich steps in float32 (peps_set_fused_steps(ctx, 0)
         // keeps the GEMM form, with the same results)
         fuse_pairs = ar_sw == Arith::F32 && D <= 4 && c->fused_steps;
+        fuse64 = ar_sw == Arith::F64 && c->fused_steps;
         Dh.assign(Lx + 1, D); Dh[0] = Dh[Lx] = 1;
         Dv.assign(Ly + 1, D); Dv[0] = Dv[Ly] = 1;
         chiU.assign(Ly, std::vector<int>(Lx + 1, 1));
@@ -910,11 +911,81 @@ public:
         return timed(PEPS_KC_FUSED, fl, [&] { return launch_row_step(a, fwd, st_); });
     }
 
+    // the float64 step over column j of rows i .. i2 (i2 = i or i + 1) as one fused kernel when it
+    // fits (done = false: use the GEMMs)
+    hipError_t step64(int i, int i2, int j, Op X, int f1, int f2, Op Y, bool fwd, bool& done, const double* lin,
+                      double* lout) {
+        done = false;
+        step_rescaled = false;
+        if (!fuse64 || X.f32 || Y.f32) return hipSuccess;
+        const bool pair = i2 != i;
+        const long long cu = chiU[i][j], cu1 = chiU[i][j + 1], cl = chiL[i2][j], cl1 = chiL[i2][j + 1];
+        const int Du = Dv[i], Dm = Dv[i + 1], Dq = Dv[i2 + 1], h = Dh[j], h1 = Dh[j + 1];
+        const Op U = envU(i, j), L = envL(i2, j), S1 = site_op(i, j), S2 = site_op(i2, j);
+        const long long hb = pair ? h : 1, hb1 = pair ? h1 : 1;
+        const int left = (int)D3, up = (int)D2, right = D, low = 1;
+        StepArgs a{};
+        a.pair = pair;
+        a.q_outer = !fwd;
+        a.X = X.p; a.xs = X.bs; a.Y = Y.p; a.ys = Y.bs;
+        a.slice = D4;
+        a.sel_bs = N;
+        if (fwd) {
+            a.F = (int)cu; a.F1 = (int)cu1; a.G = (int)cl; a.G1 = (int)cl1; a.H = h; a.H1 = h1;
+            a.Du = Du; a.Dm = Dm; a.Dq = Dq;
+            a.xf = h * hb * cl; a.xb = hb * cl; a.xb2 = cl; a.xg = 1;
+            a.yf = h1 * hb1 * cl1; a.ya = hb1 * cl1; a.ya2 = cl1; a.yg = 1;
+            a.E1 = U.p; a.e1s = U.bs; a.e1f = Du * cu1; a.e1u = cu1; a.e1f1 = 1;
+            a.E2 = L.p; a.e2s = L.bs; a.e2g = Dq * cl1; a.e2q = cl1; a.e2g1 = 1;
+            a.SA = S1.p; a.SB = S2.p;
+            a.sak[0] = a.sbk[0] = left; a.sak[1] = a.sbk[1] = up;
+            a.san[0] = a.sbn[0] = right; a.san[1] = a.sbn[1] = low;
+            a.selA = Scur + (long long)i * Lx + j; a.selB = Scur + (long long)i2 * Lx + j;
+            a.flipA = f1; a.flipB = f2;
+        } else {
+            // the same chain from the lower right: bonds of the lower environment first, the
+            // row below first, right legs in place of left ones
+            a.F = (int)cl1; a.F1 = (int)cl; a.G = (int)cu1; a.G1 = (int)cu; a.H = h1; a.H1 = h;
+            a.Du = Dq; a.Dm = pair ? Dm : Du; a.Dq = Du;
+            a.xf = 1; a.xg = h1 * hb1 * cl1;
+            a.xb = cl1; a.xb2 = h1 * cl1;
+            a.yf = 1; a.yg = h * hb * cl;
+            a.ya = cl; a.ya2 = h * cl;
+            a.E1 = L.p; a.e1s = L.bs; a.e1f = 1; a.e1u = cl1; a.e1f1 = Dq * cl1;
+            a.E2 = U.p; a.e2s = U.bs; a.e2g = 1; a.e2q = cu1; a.e2g1 = Du * cu1;
+            a.SA = S2.p; a.SB = S1.p;
+            a.sak[0] = a.sbk[0] = right; a.sak[1] = a.sbk[1] = low;
+            a.san[0] = a.sbn[0] = left; a.san[1] = a.sbn[1] = up;
+            a.selA = Scur + (long long)i2 * Lx + j; a.selB = Scur + (long long)i * Lx + j;
+            a.flipA = pair ? f2 : f1; a.flipB = f1;
+        }
+        if (!step64_fits(a)) return hipSuccess;
+        const long long nl = cu * h * hb * cl, nr = cu1 * h1 * hb1 * cl1;
+        if (!bounds_ok("step in", X, (fwd ? nl : nr) - 1, 0) || !bounds_ok("step out", Y, (fwd ? nr : nl) - 1, 0) ||
+            !bounds_ok("step U", U, cu * Du * cu1 - 1, 0) || !bounds_ok("step L", L, cl * Dq * cl1 - 1, 0))
+            return hipErrorInvalidValue;
+        done = true;
+        if (dry) return hipSuccess;
+        a.batch = Bcur;
+        a.skip = skip_; a.skip_bs = skip_bs_;
+        if (lout && step64_rescales(a)) {
+            a.lin = lin;
+            a.lout = lout;
+            step_rescaled = true;
+        }
+        double fl = (double)a.H * hb_of(a) * a.G * a.Du * a.F1 * a.F + (double)hb_of(a) * a.G * a.F1 * a.H1 * a.Dm * a.H * a.Du;
+        if (pair) fl += (double)a.G * a.F1 * a.H1 * a.H1 * a.Dq * a.H * a.Dm;
+        fl += (double)a.F1 * a.H1 * (pair ? a.H1 : 1) * a.G1 * a.G * (pair ? a.Dq : a.Dm);
+        return timed(PEPS_KC_FUSED, 2.0 * active_samples() * fl, [&] { return launch_step64(a, st_); });
+    }
+    static double hb_of(const StepArgs& a) { return a.pair ? a.H : 1; }
+
     // P_{j+1} = step(P_j) of the row-i sandwich <U_i| row i |L_i>
     hipError_t row_fwd(int i, int j, Op P, int flip, Op Pout, const double* lin = nullptr,
                        double* lout = nullptr) {
         bool done = false;
-        CK(row_fused(i, j, P, flip, Pout, true, done, lin, lout));
+        if (fuse64) CK(step64(i, i, j, P, flip, flip, Pout, true, done, lin, lout));
+        else CK(row_fused(i, j, P, flip, Pout, true, done, lin, lout));
         if (done) return hipSuccess;
         step_rescaled = false;
         const long long cu = chiU[i][j], cu1 = chiU[i][j + 1], cl = chiL[i][j], cl1 = chiL[i][j + 1];
@@ -934,7 +1005,8 @@ public:
     hipError_t row_bwd(int i, int j, Op Q, int flip, Op Qout, const double* lin = nullptr,
                        double* lout = nullptr) {
         bool done = false;
-        CK(row_fused(i, j, Q, flip, Qout, false, done, lin, lout));
+        if (fuse64) CK(step64(i, i, j, Q, flip, flip, Qout, false, done, lin, lout));
+        else CK(row_fused(i, j, Q, flip, Qout, false, done, lin, lout));
         if (done) return hipSuccess;
         step_rescaled = false;
         const long long cu = chiU[i][j], cu1 = chiU[i][j + 1], cl = chiL[i][j], cl1 = chiL[i][j + 1];
@@ -990,7 +1062,8 @@ public:
     hipError_t pair_fwd(int i, int j, Op P, int f1, int f2, Op Pout, const double* lin = nullptr,
                         double* lout = nullptr) {
         bool done = false;
-        CK(pair_fused(i, j, P, f1, f2, Pout, true, done, lin, lout));
+        if (fuse64) CK(step64(i, i + 1, j, P, f1, f2, Pout, true, done, lin, lout));
+        else CK(pair_fused(i, j, P, f1, f2, Pout, true, done, lin, lout));
         if (done) return hipSuccess;
         step_rescaled = false;
         const long long cu = chiU[i][j], cu1 = chiU[i][j + 1], cl = chiL[i + 1][j], cl1 = chiL[i + 1][j + 1];
@@ -1013,7 +1086,8 @@ public:
     hipError_t pair_bwd(int i, int j, Op Q, int f1, int f2, Op Qout, const double* lin = nullptr,
                         double* lout = nullptr) {
         bool done = false;
-        CK(pair_fused(i, j, Q, f1, f2, Qout, false, done, lin, lout));
+        if (fuse64) CK(step64(i, i + 1, j, Q, f1, f2, Qout, false, done, lin, lout));
+        else CK(pair_fused(i, j, Q, f1, f2, Qout, false, done, lin, lout));
         if (done) return hipSuccess;
         step_rescaled = false;
         const long long cu = chiU[i][j], cu1 = chiU[i][j + 1], cl = chiL[i + 1][j], cl1 = chiL[i + 1][j + 1];
@@ -1311,7 +1385,7 @@ public:
         o_zero, o_ratio, o_delta, o_flags, o_eloc, o_acc, o_G1, o_G0, o_gws;
     long long s_R, s_Y, s_G, s_svd, s_T, s_F, s_eig = 1;
     size_t o_eig = 0;
-    bool fuse_pairs = false;
+    bool fuse_pairs = false, fuse64 = false;   // float32 and float64 sandwich steps as one kernel
     int sweeps = 0;                         // variational compression sweeps (0: SVD truncation)
     std::vector<char> vcU, vcL;             // which truncations are variational
     std::vector<char> trU, trL;             // which run in trunc_step_f64

@@ -118,3 +118,25 @@ def test_register_products_equal_staged(case, tmp_path):
     assert keys
     for x, y in zip(got, base):
         assert np.array_equal(x, y)
+
+
+# the fused float64 sandwich steps against their GEMM form, both of which sum every output in
+# one order: one workgroup per sample (rescaling in the kernel) and several, a last block of
+# fewer free bond values, legs of 1 at the edges, bonds up to the last that one workgroup's
+# scratch holds and past it, and legs beyond the fused form
+@pytest.mark.parametrize("case", [(3, 3, 2, 2, 1), (4, 4, 2, 5, 700), (5, 4, 3, 9, 37), (4, 5, 3, 23, 9),
+                                  (5, 5, 4, 13, 33), (6, 4, 4, 16, 5), (4, 4, 4, 33, 6), (4, 4, 4, 64, 3),
+                                  (4, 3, 5, 20, 4), (2, 4, 4, 16, 6), (4, 2, 3, 9, 6)])
+def test_fused_float64_steps_equal_products(case):
+    Lx, Ly, D, Dc, batch = case
+    p, lat = _peps(), Lattice(Lx, Ly, D, Dc)
+    A, S = make_random(lat, batch, 500 + D)
+    Ad, Sd = _dev(A, S)
+    base = [t.cpu().numpy() for t in p.evaluate(Ad, Sd, lat, "f64", grad_mode=1)]
+    p.set_fused_steps(False)
+    try:
+        got = [t.cpu().numpy() for t in p.evaluate(Ad, Sd, lat, "f64", grad_mode=1)]
+    finally:
+        p.set_fused_steps(True)
+    for x, y in zip(got, base):
+        assert np.array_equal(x, y, equal_nan=True)

@@ -49,6 +49,9 @@ struct peps_ctx {
     uint32_t prof_mask = 0;          // bit per kernel class (PEPS_KC_*) to time
     std::vector<ProfRec> prof;
     std::vector<hipEvent_t> ev_pool;
+    // the lower boundary sweep of an evaluation runs beside the upper one (Runner::side_stream)
+    hipStream_t side = nullptr;
+    hipEvent_t side_ev[2] = {nullptr, nullptr};
     hipStream_t stream = nullptr;
     char* ws = nullptr;
     size_t ws_bytes = 0;
@@ -119,6 +122,15 @@ inline Idx2 I2(int inner, long long so, long long si) { return Idx2{inner, so, s
 struct Trunc {
     std::vector<int> chi, K, rho, tau;
     int pin = 1, p = 1;
+};
+
+// workspace offsets of one boundary sweep in float64 (the truncation, or the variational
+// compression with its overlap environments, temporaries, site tensor and factor)
+struct SweepBufs {
+    bool tr_any = false, vc_any = false;
+    size_t Y = 0, Xc = 0, tauc = 0, wyc = 0, S1 = 0, Fc = 0, Hc[2] = {0, 0}, tr = 0;
+    std::vector<size_t> Rc;
+    size_t vL = 0, vR = 0, vZ1 = 0, vZ2 = 0, vM = 0, vRf = 0, vW = 0;
 };
 
 struct Layout {
@@ -321,17 +333,18 @@ public:
             if (need_L)
                 for (int i = Ly - 1; i >= 1; --i)
                     if (trL[i]) visit_tr(tL[i]);
-            o_Rc.assign(Lx + 1, 0);
+            sweep.Rc.assign(Lx + 1, 0);
+            sweep.tr_any = any;
             if (any) {
-                o_Xc = L.alloc(s_Xc);
-                o_tauc = L.alloc(s_tauc);
-                o_wyc = s_wyc > 0 ? L.alloc(s_wyc) : 0;
-                for (int c = 1; c < Lx; ++c) o_Rc[c] = L.alloc(s_Rc[c]);
-                o_S1 = L.alloc(s_S1);
-                o_Fc = L.alloc(s_Fc);
-                o_Hc[0] = L.alloc(s_Hc);
-                o_Hc[1] = L.alloc(s_Hc);
-                o_tr = L.alloc(s_tr);
+                sweep.Xc = L.alloc(s_Xc);
+                sweep.tauc = L.alloc(s_tauc);
+                sweep.wyc = s_wyc > 0 ? L.alloc(s_wyc) : 0;
+                for (int c = 1; c < Lx; ++c) sweep.Rc[c] = L.alloc(s_Rc[c]);
+                sweep.S1 = L.alloc(s_S1);
+                sweep.Fc = L.alloc(s_Fc);
+                sweep.Hc[0] = L.alloc(s_Hc);
+                sweep.Hc[1] = L.alloc(s_Hc);
+                sweep.tr = L.alloc(s_tr);
             }
         }
         // variational compression: overlap environments L_c and R_c per cut c ([c][a][l],
@@ -361,13 +374,14 @@ public:
                     if (vcL[i]) { visit_vc(tL[i]); any = true; }
             for (int c = 0; c <= Lx; ++c) vc_eoff[c + 1] = vc_eoff[c] + e[c];
             s_vE = vc_eoff[Lx + 1];
-            o_vL = any ? L.alloc(s_vE) : 0;
-            o_vR = any ? L.alloc(s_vE) : 0;
-            o_vZ1 = any ? L.alloc(s_vZ1) : 0;
-            o_vZ2 = any ? L.alloc(s_vZ2) : 0;
-            o_vM = any ? L.alloc(s_vM) : 0;
-            o_vRf = any ? L.alloc(s_vRf) : 0;
-            o_vW = s_vW > 0 ? L.alloc(s_vW) : 0;   // factorisations beyond LDS
+            sweep.vc_any = any;
+            sweep.vL = any ? L.alloc(s_vE) : 0;
+            sweep.vR = any ? L.alloc(s_vE) : 0;
+            sweep.vZ1 = any ? L.alloc(s_vZ1) : 0;
+            sweep.vZ2 = any ? L.alloc(s_vZ2) : 0;
+            sweep.vM = any ? L.alloc(s_vM) : 0;
+            sweep.vRf = any ? L.alloc(s_vRf) : 0;
+            sweep.vW = s_vW > 0 ? L.alloc(s_vW) : 0;   // factorisations beyond LDS
         }
         o_X.resize(Lx); o_tau.resize(Lx); o_wy.assign(Lx, 0);
         for (int j = 0; j < Lx; ++j) {
@@ -378,7 +392,7 @@ public:
         o_vc = s_vc > 0 ? L.alloc(s_vc) : 0;
         o_wq = s_wq > 0 ? L.alloc(s_wq) : 0;
         o_R[0] = L.alloc(s_R); o_R[1] = L.alloc(s_R);
-        o_Y = L.alloc(s_Y);
+        sweep.Y = L.alloc(s_Y);
         o_G[0] = L.alloc(s_G); o_G[1] = L.alloc(s_G);
         o_svd = s_svd ? L.alloc(s_svd) : 0;
         s_eig = 1;
@@ -394,6 +408,7 @@ public:
             for (int i = Ly - 1; i >= 1; --i)
                 if (!vcL[i] && !trL[i]) visit_eig(tL[i]);
         o_eig = L.alloc(s_eig);
+        const size_t sandwich = L.bytes;   // from here to o_Gf: unused during the boundary sweeps
         // single-row partials
         s_P.assign(Lx + 1, 1);
         for (int i = 0; i < Ly; ++i)
@@ -444,6 +459,7 @@ public:
         for (int k = 0; k < 3; ++k) o_T[k] = L.alloc(s_T);
         o_F = L.alloc(s_F);
         o_Gf = L.alloc(s_F);
+        side_fits = need_L && side_layout(sandwich);
         o_lnW = L.alloc(1); o_sgW = L.alloc(1);
         o_lnW2 = L.alloc(1); o_sgW2 = L.alloc(1);
         o_lnWf = L.alloc(1); o_sgWf = L.alloc(1);
@@ -460,6 +476,65 @@ public:
         o_G0 = want_g ? L.alloc(0, 2LL * N * D4) : 0;
         // partial sums of the batch reduction: 2 x grad_parts(Bc) partitions of 2 N D^4
         o_gws = want_g ? L.alloc((4LL * N * D4 + kGradParts - 1) / kGradParts + 1, 4LL * N * D4) : 0;
+    }
+
+    // The boundary-sweep buffers once more, for the lower sweep beside the upper one, over the
+    // buffers that the sandwiches use later: no memory of its own.  False where they do not
+    // fit there, or where a sweep takes the float32 modes' factorisations.
+    bool side_layout(size_t at) {
+        for (int i = 0; i + 1 < Ly; ++i)
+            if (!(vcU[i] || trU[i]) || !(vcL[i + 1] || trL[i + 1])) return false;
+        Layout a;
+        a.bytes = at;
+        a.Bc = Bc;
+        SweepBufs& o = side_bufs;
+        o = sweep;
+        o.Y = a.alloc(s_Y);
+        if (sweep.tr_any) {
+            o.Xc = a.alloc(s_Xc);
+            o.tauc = a.alloc(s_tauc);
+            o.wyc = s_wyc > 0 ? a.alloc(s_wyc) : 0;
+            for (int c = 1; c < Lx; ++c) o.Rc[c] = a.alloc(s_Rc[c]);
+            o.S1 = a.alloc(s_S1);
+            o.Fc = a.alloc(s_Fc);
+            o.Hc[0] = a.alloc(s_Hc);
+            o.Hc[1] = a.alloc(s_Hc);
+            o.tr = a.alloc(s_tr);
+        }
+        if (sweep.vc_any) {
+            o.vL = a.alloc(s_vE);
+            o.vR = a.alloc(s_vE);
+            o.vZ1 = a.alloc(s_vZ1);
+            o.vZ2 = a.alloc(s_vZ2);
+            o.vM = a.alloc(s_vM);
+            o.vRf = a.alloc(s_vRf);
+            o.vW = s_vW > 0 ? a.alloc(s_vW) : 0;
+        }
+        return a.bytes <= L.bytes;
+    }
+
+    // The stream of the lower sweep when it may run beside the upper one, else null (one after
+    // the other on the caller's stream): not under capture, in the allocation-free entry point
+    // or while kernels are timed or tuned.
+    hipStream_t side_stream() {
+        if (!side_fits || dry || quiet || ctx->prof_mask || ctx->tune_mode) return nullptr;
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st_, &cs) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        if (cs != hipStreamCaptureStatusNone) return nullptr;
+        for (auto& e : ctx->side_ev)
+            if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+                e = nullptr;
+                (void)hipGetLastError();
+                return nullptr;
+            }
+        if (!ctx->side && hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess) {
+            ctx->side = nullptr;
+            (void)hipGetLastError();
+        }
+        return ctx->side;
     }
 
     static size_t lds_cap_bytes();
@@ -603,7 +678,7 @@ public:
             Op Rin = (j == 0) ? ones() : op(o_R[(j - 1) & 1], s_R);
             const long long ldR = t.K[j];
             Op Ein = down ? envU(row, j) : envL(row, j);
-            Op Y = tmp(o_Y, s_Y, ar);
+            Op Y = tmp(sweep.Y, s_Y, ar);
             // Y[(a',l),(u,b)] = sum_a R[a', a*Dl+l] E[a,(u,b)]
             CK(gemm_a(ar, rho * Dl, pin * chj1, chj, Rin, I2(Dl, ldR, 1), I1(Dl), Gather{},
                     Ein, I1((long long)pin * chj1), I1(1), Gather{},
@@ -699,12 +774,12 @@ public:
         const Arith F64 = Arith::F64;
         auto Ein = [&](int j) { return down ? envU(row, j) : envL(row, j); };
         auto Eout = [&](int j) { return down ? envU(row + 1, j) : envL(row - 1, j); };
-        auto Rcut = [&](int c) { return c == 0 ? ones() : op(o_Rc[c], s_Rc[c]); };
+        auto Rcut = [&](int c) { return c == 0 ? ones() : op(sweep.Rc[c], s_Rc[c]); };
         for (int j = 0; j + 1 < Lx; ++j) {
             const int chj = t.chi[j], chj1 = t.chi[j + 1], Dl = Dh[j], Dr = Dh[j + 1];
             const int rho = t.rho[j], cols = t.K[j + 1];
             const long long rows = (long long)rho * p;
-            const Op Y = op(o_Y, s_Y), X = op(o_Xc, s_Xc), R = Rcut(j + 1);
+            const Op Y = op(sweep.Y, s_Y), X = op(sweep.Xc, s_Xc), R = Rcut(j + 1);
             // Y[(a',l),(u,b)] = sum_a R[a', a*Dl+l] E[a,(u,b)]
             CK(gemm_a(F64, rho * Dl, pin * chj1, chj, Rcut(j), I2(Dl, t.K[j], 1), I1(Dl), Gather{}, Ein(j),
                       I1((long long)pin * chj1), I1(1), Gather{}, Y, I1((long long)pin * chj1), I1(1)));
@@ -724,16 +799,16 @@ public:
             }
             KL(timed(PEPS_KC_QR, Bcur * qr_flops((double)rows, cols), [&] {
                 if (blocked)
-                    return launch_qr_r(X.p, X.bs, (int)rows, cols, R.p, R.bs, buf(o_wyc), s_wyc, Bcur, st_);
-                return launch_qr(X.p, X.bs, (int)rows, cols, R.p, R.bs, buf(o_tauc), s_tauc, Bcur, st_);
+                    return launch_qr_r(X.p, X.bs, (int)rows, cols, R.p, R.bs, buf(sweep.wyc), s_wyc, Bcur, st_);
+                return launch_qr(X.p, X.bs, (int)rows, cols, R.p, R.bs, buf(sweep.tauc), s_tauc, Bcur, st_);
             }));
         }
         int cur = 0;
         for (int j = Lx - 1; j >= 0; --j) {
             const int chj = t.chi[j], chj1 = t.chi[j + 1], Dl = Dh[j], Dr = Dh[j + 1];
             const int tin = t.tau[j + 1], np = p * tin, rho = t.rho[j], K = t.K[j];
-            const Op H = j + 1 == Lx ? ones() : op(o_Hc[cur], s_Hc), S1 = op(o_S1, s_S1);
-            const Op F = j == 0 ? Eout(0) : op(o_Fc, s_Fc);
+            const Op H = j + 1 == Lx ? ones() : op(sweep.Hc[cur], s_Hc), S1 = op(sweep.S1, s_S1);
+            const Op F = j == 0 ? Eout(0) : op(sweep.Fc, s_Fc);
             // S1[(a,u),(r,t)] = sum_b E[a,u,b] H[(b,r),t]
             CK(gemm_a(F64, chj * pin, Dr * tin, chj1, Ein(j), I1(chj1), I1(1), Gather{}, H, I1(Dr * tin), I1(1),
                       Gather{}, S1, I1(Dr * tin), I1(1)));
@@ -742,7 +817,7 @@ public:
                       I2(Dr, (long long)Dr * tin, tin), Gather{}, site_op(row, j), I2(Dr, s_in, D),
                       I2(p, D3, s_out), site_gather(row, j, 0), F, I2(tin, (long long)Dl * np, 1), I2(p, np, tin)));
             if (j == 0) break;
-            const Op M = op(o_tr, s_tr), Hn = op(o_Hc[cur ^ 1], s_Hc), En = Eout(j);
+            const Op M = op(sweep.tr, s_tr), Hn = op(sweep.Hc[cur ^ 1], s_Hc), En = Eout(j);
             CK(gemm_a(F64, rho, np, K, Rcut(j), I1(K), I1(1), Gather{}, F, I1(np), I1(1), Gather{}, M, I1(np), I1(1)));
             if ((long long)trunc_scratch_doubles(rho, np, Dc) > s_tr || !trunc_fits(rho, np, Dc) ||
                 !bounds_ok("truncation V", En, (long long)t.tau[j] * np - 1, 0) ||
@@ -778,15 +853,15 @@ public:
         const Arith F = Arith::F64;
         auto Ein = [&](int j) { return down ? envU(row, j) : envL(row, j); };
         auto Cout = [&](int j) { return down ? envU(row + 1, j) : envL(row - 1, j); };
-        auto Lenv = [&](int c) { return c == 0 ? ones() : op(o_vL, s_vE).at(vc_eoff[c]); };
-        auto Renv = [&](int c) { return c == Lx ? ones() : op(o_vR, s_vE).at(vc_eoff[c]); };
-        const Op Z1 = op(o_vZ1, s_vZ1), Z2 = op(o_vZ2, s_vZ2), Mb = op(o_vM, s_vM), Rf = op(o_vRf, s_vRf);
+        auto Lenv = [&](int c) { return c == 0 ? ones() : op(sweep.vL, s_vE).at(vc_eoff[c]); };
+        auto Renv = [&](int c) { return c == Lx ? ones() : op(sweep.vR, s_vE).at(vc_eoff[c]); };
+        const Op Z1 = op(sweep.vZ1, s_vZ1), Z2 = op(sweep.vZ2, s_vZ2), Mb = op(sweep.vM, s_vM), Rf = op(sweep.vRf, s_vRf);
         const Op lin = down ? logU(row) : logL(row), lout = down ? logU(row + 1) : logL(row - 1);
         // thin QR of an m x n column-major matrix at X into Q (rows q_row, columns q_col apart)
         auto thinq = [&](const Op& X, int m, int n, const Op& Q, long long q_row, long long q_col,
                          bool with_r) -> hipError_t {
             const bool on_chip = !thinq_needs_scratch(m, n);   // registers or LDS: no scratch
-            const Op Wq = op(o_vW, s_vW);
+            const Op Wq = op(sweep.vW, s_vW);
             if (!bounds_ok("vc qr in", X, (long long)m * n - 1, 0) ||
                 !bounds_ok("vc qr out", Q, (long long)(m - 1) * q_row + (long long)(n - 1) * q_col, 0) ||
                 (with_r && !bounds_ok("vc qr R", Rf, (long long)n * n - 1, 0)) ||
@@ -1210,11 +1285,33 @@ public:
             if (down ? vcU[i] : vcL[i]) return vc_step(down, i);
             return (down ? trU[i] : trL[i]) ? trunc_step_f64(down, i) : trunc_step(down, i);
         };
-        for (int i = 0; i + 1 < Ly; ++i) CK(boundary(true, i));
         const bool need_L = want_eloc || want_grad;
-        if (need_L) {
-            KL(launch_fill(buf(o_logL[Ly - 1]), Bn, 0.0, st));
-            for (int i = Ly - 1; i >= 1; --i) CK(boundary(false, i));
+        if (need_L) KL(launch_fill(buf(o_logL[Ly - 1]), Bn, 0.0, st));
+        if (hipStream_t side = need_L ? side_stream() : nullptr) {
+            // The lower sweep beside the upper one, row by row in turn: both are chains of
+            // factorisations that leave most of the device idle at tens of samples.  12x12 D = 6,
+            // 48 samples, the whole evaluation 412 -> 280 ms; 8x8 D = 4, 512 samples 38 -> 31 ms.
+            // Joined also after an error.
+            CK(hipEventRecord(ctx->side_ev[0], st));
+            CK(hipStreamWaitEvent(side, ctx->side_ev[0], 0));
+            hipError_t e = hipSuccess;
+            for (int i = 0; i + 1 < Ly && e == hipSuccess; ++i) {
+                e = boundary(true, i);
+                if (e != hipSuccess) break;
+                std::swap(sweep, side_bufs);
+                st_ = side;
+                e = boundary(false, Ly - 1 - i);
+                std::swap(sweep, side_bufs);
+                st_ = st;
+            }
+            hipError_t j = hipEventRecord(ctx->side_ev[1], side);
+            if (j == hipSuccess) j = hipStreamWaitEvent(st, ctx->side_ev[1], 0);
+            CK(e);
+            CK(j);
+        } else {
+            for (int i = 0; i + 1 < Ly; ++i) CK(boundary(true, i));
+            if (need_L)
+                for (int i = Ly - 1; i >= 1; --i) CK(boundary(false, i));
         }
         if (want_grad) KL(launch_fill(buf(o_delta), (long long)Bn * N * D4, 0.0, st));
         const int nH = Ly * (Lx - 1), nV = (Ly - 1) * Lx, nD = (Ly - 1) * (Lx - 1);
@@ -1381,7 +1478,7 @@ public:
     int skip_bond_ = -1;
     std::vector<int8_t> act_host_;
     bool quiet = false;       // no profiling events (the allocation-free entry point)
-    size_t o_R[2], o_G[2], o_Y, o_svd, o_T[3], o_F, o_Gf, o_lnW, o_sgW, o_lnW2, o_sgW2, o_lnWf, o_sgWf,
+    size_t o_R[2], o_G[2], o_svd, o_T[3], o_F, o_Gf, o_lnW, o_sgW, o_lnW2, o_sgW2, o_lnWf, o_sgWf,
         o_zero, o_ratio, o_delta, o_flags, o_eloc, o_acc, o_G1, o_G0, o_gws;
     long long s_R, s_Y, s_G, s_svd, s_T, s_F, s_eig = 1;
     size_t o_eig = 0;
@@ -1390,11 +1487,11 @@ public:
     std::vector<char> vcU, vcL;             // which truncations are variational
     std::vector<char> trU, trL;             // which run in trunc_step_f64
     std::vector<long long> s_Rc;
-    std::vector<size_t> o_Rc;
-    size_t o_Xc = 0, o_tauc = 0, o_wyc = 0, o_S1 = 0, o_Fc = 0, o_Hc[2] = {0, 0}, o_tr = 0;
+    // buffers of one boundary sweep, and those of the sweep on the side stream
+    SweepBufs sweep, side_bufs;
+    bool side_fits = false;
     long long s_Xc = 0, s_tauc = 0, s_wyc = 0, s_S1 = 0, s_Fc = 0, s_Hc = 0, s_tr = 0;
     std::vector<long long> vc_eoff;         // offset of cut c's overlap environment
-    size_t o_vL = 0, o_vR = 0, o_vZ1 = 0, o_vZ2 = 0, o_vM = 0, o_vRf = 0, o_vW = 0;
     long long s_vE = 0, s_vZ1 = 0, s_vZ2 = 0, s_vM = 0, s_vRf = 0, s_vW = 0;
     bool step_rescaled = false;   // the last sandwich step also applied the max-abs rescale
 };
@@ -1468,6 +1565,12 @@ peps_status peps_destroy(peps_ctx* c) {
     if (c->stream) hipStreamSynchronize(c->stream);
     else hipDeviceSynchronize();
     drop_graphs(c);
+    if (c->side) {
+        hipStreamSynchronize(c->side);
+        hipStreamDestroy(c->side);
+    }
+    for (auto e2 : c->side_ev)
+        if (e2) hipEventDestroy(e2);
     for (auto s2 : c->job_streams) hipStreamDestroy(s2);
     for (auto e2 : c->job_events) hipEventDestroy(e2);
     if (c->ws) hipFree(c->ws);

@@ -760,9 +760,9 @@ __device__ __forceinline__ void block_orth(double* X, int m, int tk, double (*vb
 #pragma unroll
         for (int r = 0; r < RPL; ++r) a[s][r] = __builtin_amdgcn_ldexp(a[s][r], ex);
     }
-    thinq_factor<NW, SL, RPL>(a, m, tk, vbuf, tau);
+    thinq_factor<NW, SL, RPL>(a, tk, vbuf, tau);
     __syncthreads();
-    thinq_form<NW, SL, RPL>(a, m, tk, vbuf, tau);
+    thinq_form<NW, SL, RPL>(a, tk, vbuf, tau);
 #pragma unroll
     for (int s = 0; s < SL; ++s) {
         const int j = s * NW + w;

@@ -1,7 +1,7 @@
 // Kernels of the variational boundary compression (one-site alternating least squares,
 // the truncation alternative of Sec. II-A): the thin QR that turns an updated site
 // tensor into an isometry, and the normalisation of the final site.  The contractions
-// of the sweeps are batched GEMMs (k_mgemm.hip).
+// of the sweeps are batched GEMMs (k_dgemm.hip).
 #include "common.h"
 #include "kernels.h"
 #include "thinq.h"
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(NW * 64) void k_thinq_reg(const double* X, long lon
             a[s][r] = (j < n && i < m) ? Xb[i + (long long)j * m] : 0.0;
         }
     }
-    thinq_factor<NW, SL, RPL>(a, m, n, vbuf, tau);
+    thinq_factor<NW, SL, RPL>(a, n, vbuf, tau);
     // signs of diag(R) and R itself
 #pragma unroll
     for (int s = 0; s < SL; ++s) {
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(NW * 64) void k_thinq_reg(const double* X, long lon
             }
         }
     }
-    thinq_form<NW, SL, RPL>(a, m, n, vbuf, tau);
+    thinq_form<NW, SL, RPL>(a, n, vbuf, tau);
     double* Qb = Q + (long long)b * qs;
 #pragma unroll
     for (int s = 0; s < SL; ++s) {
@@ -201,8 +201,9 @@ bool thinq_needs_scratch(int m, int n) {
     return !(m <= 256 && n <= 40) && !(m <= 512 && n <= 64) && !thinq_fits(m, n);
 }
 
-// Up to 256 x 40 and 512 x 64: in registers (512 and 1024 threads); beyond, in LDS where
-// it fits (256 threads, one column per wave at a time), else in global scratch (1024
+// Up to 256 x 40 and 512 x 64: in registers, by 512 threads while eight waves of four or five
+// columns each hold them (512 x 32, 16 matrices: 43 us, 66 by 1024 threads, whose second wave
+// per SIMD only adds to the steps), else by 1024; beyond, in LDS where it fits (256 threads, one column per wave at a time), else in global scratch (1024
 // threads and four columns per wave, so that every trailing column group of a step has a
 // wave of its own and each load of v serves four columns)
 hipError_t launch_thinq(const double* X, long long xs, int m, int n, double* Q, long long qs, long long q_row,
@@ -212,6 +213,9 @@ hipError_t launch_thinq(const double* X, long long xs, int m, int n, double* Q, 
     if (!thinq_shape_ok(m, n)) return hipErrorInvalidValue;
     if (m <= 256 && n <= 40) {
         hipLaunchKernelGGL((k_thinq_reg<8, 5, 4>), dim3(batch), dim3(512), 0, st, X, xs, m, n, Q, qs, q_row, q_col,
+                           R, rs);
+    } else if (m <= 512 && n <= 32) {
+        hipLaunchKernelGGL((k_thinq_reg<8, 4, 8>), dim3(batch), dim3(512), 0, st, X, xs, m, n, Q, qs, q_row, q_col,
                            R, rs);
     } else if (m <= 512 && n <= 64) {
         hipLaunchKernelGGL((k_thinq_reg<16, 4, 8>), dim3(batch), dim3(1024), 0, st, X, xs, m, n, Q, qs, q_row, q_col,

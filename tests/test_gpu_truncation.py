@@ -140,3 +140,23 @@ def test_fused_float64_steps_equal_products(case):
         p.set_fused_steps(True)
     for x, y in zip(got, base):
         assert np.array_equal(x, y, equal_nan=True)
+
+
+# site factorisations of the variational compression at the edges of their register blockings
+# (256 x 40, 512 x 32 and 512 x 64; n = 8, 16, 32 and 40 are whole slots of eight waves)
+@pytest.mark.parametrize("case", [(4, 4, 7, 36), (4, 4, 7, 37), (4, 4, 8, 32), (4, 4, 10, 30), (4, 4, 12, 33),
+                                  (4, 4, 13, 20), (4, 4, 5, 8), (4, 4, 4, 9)])
+def test_register_site_factorisations(case):
+    Lx, Ly, D, Dc = case
+    p, lat = _peps(), Lattice(Lx, Ly, D, Dc)
+    A, S = _weak(lat, 2, 900 + D, 0.3 / D ** 2)
+    p.set_truncation(1)
+    try:
+        la, sg, fl = (t.cpu().numpy() for t in p.log_amplitude(*_dev(A, S), lat, "f64"))
+    finally:
+        p.set_truncation(0)
+    assert not fl.any()
+    for b in range(len(S)):
+        la_o, sg_o, fl_o = O.log_amplitude_one(A, lat, S[b], 1)
+        assert fl_o == 0 and int(sg[b]) == int(sg_o)
+        assert abs(la[b] - la_o) <= 1e-10 * max(1.0, abs(la_o))

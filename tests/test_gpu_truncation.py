@@ -160,3 +160,20 @@ def test_register_site_factorisations(case):
         la_o, sg_o, fl_o = O.log_amplitude_one(A, lat, S[b], 1)
         assert fl_o == 0 and int(sg[b]) == int(sg_o)
         assert abs(la[b] - la_o) <= 1e-10 * max(1.0, abs(la_o))
+
+
+# rescaling and overlap of partials around the 8192 entries where 1024 threads take over: two-row
+# partials of 36 36 6 6 entries, of 15 15 6 6 = 8100, 16 16 6 6 and 13 13 7 7 = 8281, against the oracle
+@pytest.mark.parametrize("case", [(4, 4, 6, 36), (4, 4, 6, 15), (4, 4, 6, 16), (4, 4, 7, 13)])
+def test_long_partials(case):
+    Lx, Ly, D, Dc = case
+    lat = Lattice(Lx, Ly, D, Dc)
+    A, S = _weak(lat, 2, 950 + D, 0.3 / D ** 2)
+    la, sg, e, g, fl = (t.cpu().numpy() for t in _peps().evaluate(*_dev(A, S), lat, "f64", grad_mode=1))
+    assert not fl.any()
+    for b in range(len(S)):
+        la_o, sg_o, e_o, d_o, fl_o = O.full_path_one(A, lat, S[b])
+        assert fl_o == 0 and int(sg[b]) == int(sg_o)
+        assert abs(la[b] - la_o) <= 1e-10 * max(1.0, abs(la_o))
+        assert abs(e[b] - e_o) <= 1e-9 * max(1.0, abs(e_o))
+        assert np.linalg.norm(g[b] - d_o) <= 1e-9 * np.linalg.norm(d_o)

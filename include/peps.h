@@ -98,9 +98,9 @@ peps_status peps_set_stream(peps_ctx* ctx, void* hip_stream);
  * PEPS_ERR_INVALID_ARG for sweeps outside [0, 16]. */
 peps_status peps_set_truncation(peps_ctx* ctx, int32_t sweeps);
 
-/* Fused float32 sandwich steps (enable != 0, the default): the single- and two-row steps
- * of the float32 and bfloat16 modes with legs <= 4 and boundary bonds <= 16 run as one
- * kernel each, summing every product in the order of the GEMM form, so their results
+/* Fused sandwich steps (enable != 0, the default): the single- and two-row steps
+ * of the float32 and bfloat16 modes with legs <= 4 and boundary bonds <= 16, and of the
+ * float64 mode with legs <= 4 and bonds that fit the chip, run as one kernel each, summing every product in the order of the GEMM form, so their results
  * equal the GEMM form's bit for bit.  enable = 0 keeps the GEMM form (a comparison
  * switch; slower). */
 peps_status peps_set_fused_steps(peps_ctx* ctx, int32_t enable);

@@ -500,6 +500,10 @@ hipError_t launch_mgemm(const GemmArgs& g, Arith ar, hipStream_t st, int tile) {
     // product, whose stores then coalesce.  Same products, same ascending k: same bits.
     auto unit = [](const Idx2& x) { return x.s_inner == 1 && x.inner > 1; };
     if (unit(g.cm) && !unit(g.cn)) return launch_mgemm(gemm_transposed(g), ar, st, tile);
+    // the untuned choice in float64: from registers, up to 4 times as fast as the untuned choice
+    // among the tiles below on 165 of 168 products (D = 2 to 16; median 1.5), up to 7 % slower on
+    // the others (N of 32 with K of 512; 64 x 64 x 64 of thousands of samples; 4.5 us launches),
+    // which the autotuner may take from here
     if (tile <= 0 && ar == Arith::F64) {
         bool done;
         const hipError_t e = launch_dgemm(g, st, done);

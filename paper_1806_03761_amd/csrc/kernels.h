@@ -5,7 +5,7 @@
 
 namespace peps {
 
-// tile: 0 = heuristic choice, 1..kMfmaTiles = a matrix-core tile shape (k_mgemm.hip), the two
+// tile: 0 = the untuned choice (float64: k_dgemm where it fits), 1..kMfmaTiles = a matrix-core tile shape (k_mgemm.hip), the two
 // after them = the row kernel (k_gemm.hip) on the product or its transpose
 static constexpr int kMfmaTiles = 35;
 static constexpr int kGemmTiles = kMfmaTiles + 2;

@@ -58,7 +58,7 @@ struct peps_ctx {
     size_t ws_limit = 0;
     double* ones = nullptr;   // 4096 ones
     char* scratch = nullptr;  // device address of this device's fixed scratch array
-    bool fused_steps = true;  // fused float32 sandwich steps where they fit (else the GEMM form)
+    bool fused_steps = true;  // fused sandwich steps where they fit (else the GEMM form)
     int vc_sweeps = 0;        // 0: SVD truncation; n > 0: variational compression, n sweeps
     char* mc = nullptr;       // sampling buffers (peps_metropolis_step, peps_vmc_step)
     size_t mc_bytes = 0;
@@ -155,7 +155,7 @@ public:
         // environment-tensor GEMMs then run in f32 (f32 and f64 use one type throughout)
         ar = prec == PEPS_PREC_F64 ? Arith::F64 : (prec == PEPS_PREC_F32 ? Arith::F32 : Arith::BF16);
         ar_sw = prec == PEPS_PREC_F64 ? Arith::F64 : Arith::F32;
-        // fused single- and two-row sandwich steps in float32 (peps_set_fused_steps(ctx, 0)
+        // fused single- and two-row sandwich steps (peps_set_fused_steps(ctx, 0)
         // keeps the GEMM form, with the same results)
         fuse_pairs = ar_sw == Arith::F32 && D <= 4 && c->fused_steps;
         fuse64 = ar_sw == Arith::F64 && c->fused_steps;

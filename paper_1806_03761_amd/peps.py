@@ -224,7 +224,7 @@ def set_truncation(sweeps: int, device: int = 0):
 
 
 def set_fused_steps(enable: bool, device: int = 0):
-    """Fused float32 sandwich steps on (default) or the GEMM form (same results)."""
+    """Fused sandwich steps on (default) or the GEMM form (same results)."""
     lib, ctx = _context(device)
     _check(lib, ctx, lib.peps_set_fused_steps(ctx, 1 if enable else 0), "peps_set_fused_steps")
 

@@ -49,6 +49,7 @@ struct DgArgs {
     const double* B;
     double* C;
     double alpha;
+    int by_xcd;
     const int8_t* skip;
     long long skip_bs;
 };
@@ -124,10 +125,10 @@ template <int BM, int BN, int KU>
 __global__ __launch_bounds__(256, (BM * BN >= 8 ? 2 : BM * BN >= 4 ? 3 : 4)) void k_dgemm(DgArgs g) {
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, gq = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // workgroups go to the 8 XCDs in turn: each XCD takes one contiguous run of tiles, so a
-    // sample's operands are fetched into one L2 only
+    // workgroups go to the 8 XCDs in turn; g.by_xcd: each XCD takes one contiguous run of tiles, so
+    // a sample's operands are fetched into one L2 only
     const unsigned nb = gridDim.x, per = nb / 8, rem = nb % 8, x = blockIdx.x % 8, y = blockIdx.x / 8;
-    const unsigned blk = x * per + (x < rem ? x : rem) + y;
+    const unsigned blk = g.by_xcd ? x * per + (x < rem ? x : rem) + y : blockIdx.x;
     const unsigned t = blk * 4 + w, tiles = (unsigned)g.tiles_m * g.tiles_n;
     const int b = (int)(t / tiles);
     if (b >= g.batch) return;
@@ -218,8 +219,27 @@ bool make_step(const Idx2& x, int n, DStep& d, long long& bound) {
     return true;
 }
 
+// An operand whose 16 x 4 loads fall on 64 separate lines: neither the free index nor k has unit
+// stride, and a line comes back only after the `inner` values of k (the site products of a backward
+// step).  With 6 of them the lines stay in L1 and this kernel is the faster (36 x 7776 x 36, 64 samples
+// 78 us, LDS-staged 120), with 8 it is not (64 x 32768 x 64, 32 samples 357 and 345), with 16 far from
+// it (256 x 16384 x 256, 16 samples 4.8 and 2.2 ms).  Read for at most 64 rows of the other operand
+// the lines hardly come back anyway, and the more numerous waves win (32 x 512 x 512, 16 samples
+// 24 and 64 us).
+bool scattered(const Idx2& free, int n, const Idx2& k, int nk, int other) {
+    const auto inner = [](const Idx2& x, int m) { return x.inner == 1 ? m : std::min(x.inner, m); };
+    const auto stride = [](const Idx2& x) { return x.inner == 1 ? x.s_outer : x.s_inner; };
+    return other > 64 && inner(free, n) >= 8 && stride(free) > 1 && inner(k, nk) >= 8 && stride(k) > 1;
+}
+
+// Samples a multiple of 32 KB apart: runs of tiles by XCD would start on the same memory channel
+// (D = 16, bond 32, 16 samples: a product of 328 us takes 1226).  Elsewhere runs by XCD gain up to a
+// fifth (216 x 216 x 36, 256 samples 33 us, 40 in turn).
+bool camps(long long bs) { return bs != 0 && bs % 4096 == 0; }
+
 bool make_args(const GemmArgs& g, DgArgs& d) {
     if (g.a_f32 || g.b_f32 || g.c_f32 || g.beta != 0.0 || g.K <= 0) return false;
+    if (scattered(g.am, g.M, g.ak, g.K, g.N) || scattered(g.bn, g.N, g.bk, g.K, g.M)) return false;
     long long ba = 0, bb = 0, bc = 0;
     // rows are mapped up to the end of their tile on the output side (masked there)
     if (!make_map(g.am, g.M, d.am, ba) || !make_map(g.bn, g.N, d.bn, bb) || !make_map(g.cm, g.M, d.cm, bc) ||
@@ -231,6 +251,7 @@ bool make_args(const GemmArgs& g, DgArgs& d) {
     d.ga = g.ga; d.gb = g.gb; d.gc = g.gc;
     d.A = g.A; d.B = g.B; d.C = g.C;
     d.alpha = g.alpha;
+    d.by_xcd = !(camps(g.a_bs) || camps(g.b_bs) || camps(g.c_bs));
     d.skip = g.skip; d.skip_bs = g.skip_bs;
     return true;
 }

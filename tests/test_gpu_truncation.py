@@ -87,11 +87,12 @@ def test_blocked_r_factor(shape):
 
 # the float64 products computed from registers (the untuned choice) against the LDS-staged
 # kernel (tile 4), which sum every output alike: equal bits over odd legs and bonds (a K that 4
-# does not divide, split indices of 2 to 7, ragged edges of every block shape) and both
-# boundary methods
+# does not divide, split indices of 2 to 7, ragged edges of every block shape), with scattered
+# operands and samples a power of two apart, and both boundary methods
 @pytest.mark.parametrize("case", [(4, 4, 2, 3, 5, 0), (5, 4, 3, 7, 33, 0), (4, 5, 5, 17, 9, 0),
                                   (4, 3, 7, 19, 2, 0), (4, 5, 3, 9, 300, 2),
-                                  (5, 4, 6, 30, 7, 1), (4, 4, 2, 1, 700, 0)])
+                                  (5, 4, 6, 30, 7, 1), (4, 4, 2, 1, 700, 0),
+                                  (4, 4, 8, 16, 3, 0), (4, 3, 16, 12, 2, 1)])
 def test_register_products_equal_staged(case, tmp_path):
     Lx, Ly, D, Dc, batch, sweeps = case
     p, lat = _peps(), Lattice(Lx, Ly, D, Dc)

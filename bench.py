@@ -103,11 +103,11 @@ def _sources_hash() -> str:
 
 
 CLASSES = ("gemm", "fused", "qr", "svd")
-CLASS_NAMES = {"svd": "truncation step (Q application, Gram matrix, tridiagonalisation, bisection, "
+CLASS_NAMES = {"svd": "truncation step (Gram matrix, tridiagonalisation, bisection, "
                       "eigenvectors, subspace refinement)",
-               "qr": "blocked Householder QR (register panels + 32-reflector WY GEMMs)",
-               "gemm": "k_mgemm contraction GEMMs (apply, sandwiches, environments)",
-               "fused": "fused sandwich steps (k_pair_mfma / k_row_step)"}
+               "qr": "Householder QR (register panels, updates on the matrix cores)",
+               "gemm": "k_dgemm contraction GEMMs (apply, sandwiches, environments)",
+               "fused": "fused sandwich steps (k_pair_mfma / k_row_step, k_step64)"}
 
 
 def _read(peps, classes):

@@ -15,6 +15,10 @@
 // banks.  All four products run on 16x16x4 MFMAs, A operands from memory (T1) or LDS, B
 // operands from memory through L1, held in registers for T2 and T3.  Every output sums in
 // the k order of its GEMM, so the results are equal to those of the GEMM form bit for bit.
+//
+// Bound by latency at small samples, by the matrix cores and LDS at D = 4.  A step, mean over an
+// evaluation: 4x4 D = 2, 256 samples, three or four launches of 3.4 us and a rescaling of 3.2 -> 6.0 us;
+// 8x8 D = 4, bond 16, 512 samples, launches of 8 to 13 us each -> 19 us.
 #include <algorithm>
 
 #include "common.h"
@@ -26,6 +30,7 @@ namespace peps {
 namespace {
 
 constexpr int kStepNT = 256, kSite = 16, KS = kSite / 4;   // threads; K and N of a site product
+// LDS of a workgroup: four of them on a compute unit
 constexpr long long kStepLds = 40 * 1024;
 
 // division by a launch constant: i / d by multiply-high (exact while i d < 2^32)
@@ -256,6 +261,10 @@ struct StepPlan {
     bool whole;   // one workgroup per sample
 };
 
+// Site products of K and N up to 16, one MFMA tile of columns and four k steps held in registers:
+// legs up to 4.  Wider ones (D = 6: 36 x 36, 140 KB of LDS, one workgroup per compute unit) ran slower
+// than their products (12x12 evaluation 412 -> 451 ms).  A sample of at most 32 KB goes to one
+// workgroup, which then rescales it; else as many f' as fill the 16 columns of the first product.
 bool plan_of(const StepArgs& a, StepPlan& s) {
     const int hb = a.pair ? a.H : 1, hb1 = a.pair ? a.H1 : 1, dq = a.pair ? a.Dq : a.Dm;
     const int k2 = std::max(a.H * a.Du, a.pair ? a.H * a.Dm : 1), n2 = std::max(a.H1 * a.Dm, a.pair ? a.H1 * a.Dq : 1);

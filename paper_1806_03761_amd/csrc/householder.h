@@ -45,22 +45,18 @@ __device__ __forceinline__ void hh_scalars(double al, double sq, double& tk, dou
 }
 
 // The same reflector unnormalised, H = I - t u u^T with u = (al - beta, x): beta, u's pivot entry
-// and t = 1 / (norm (norm + |al|)).  A column whose squares leave the range of doubles (its
-// entries below 1e-140 of anything the callers scale to one) counts as zero below the pivot.
-__device__ __forceinline__ void hh_unnormalised(double al, double sq, double& be, double& up, double& t) {
+// and t = 1 / (norm (norm + |al|)).  False, through one scalar branch (al and sq are the same in every
+// lane), where the squared norm is near the ends of the range of doubles.
+__device__ __forceinline__ bool hh_unnormalised(double al, double sq, double& be, double& up, double& t) {
     const double s2 = fma(al, al, sq);
-    if (sq == 0.0 || s2 < 1e-280) {
-        be = al;
-        up = 0.0;
-        t = 0.0;
-    } else {
-        double r, nrm;
-        hh_norm(s2, r, nrm);
-        const double den = fabs(al) + nrm;
-        be = -copysign(nrm, al);
-        up = copysign(den, al);
-        t = r * hh_rcp(den);
-    }
+    double r, nrm;
+    hh_norm(s2, r, nrm);
+    const double den = fabs(al) + nrm;
+    const bool none = sq == 0.0;
+    be = none ? al : -copysign(nrm, al);
+    up = none ? 0.0 : copysign(den, al);
+    t = none ? 0.0 : r * hh_rcp(den);
+    return !__builtin_amdgcn_readfirstlane(!none && !(s2 > 1e-280 && s2 < 1e280));
 }
 
 }  // namespace peps

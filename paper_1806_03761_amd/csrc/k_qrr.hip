@@ -12,9 +12,8 @@
 //                 registers in the same layout, W = U^T A, A -= U (T^T W) on the matrix cores;
 //                 the block is read and written once, its first rows leave as rows of R.
 // The reflectors are left unnormalised, H = I - t u u^T with u = (alpha - beta, x): no column is
-// rescaled, T carries the factors.  R may be scaled by any power of two (the sweep uses the row
-// space of R only), so it is returned with its leading entry in [1/2, 1): the next column
-// tensor then stays in range however many columns there are.
+// rescaled, T carries the factors.  R is not rescaled either: by its leading entry, a first column
+// far below the others would carry them out of range.
 // Taller matrices are cut into blocks of up to 2048 rows, factorised side by side, and their
 // R factors, stacked, factorised again.
 //
@@ -44,9 +43,8 @@ struct QrrArgs {
     int rblk; long long rstr;        // row i lies at (i / rblk) rstr + i % rblk (rblk = 0: at i)
     double* R; long long rs, rsub;   // R of matrix b at R + (b / nsub) rs + (b % nsub) rsub, ld n
     double* V; long long vs, vsub;   // packed reflectors of the current panel, and behind them
-    long long ot;                    // (at ot) its T, 32 x 32 row-major, and the exponent of R
+    long long ot;                    // (at ot) its T, 32 x 32 row-major
     int nmat;
-    int keep_scale;                  // 1: R as it is (row blocks whose factors are stacked)
 };
 
 __device__ __forceinline__ double* qrr_v(const QrrArgs& q, int b) {
@@ -87,11 +85,12 @@ struct QrrTile {
     double *rd, *tp;   // of this tile
     int w, li, gq, row0, nref;   // row0: the tile's first pivot row inside the panel (a multiple of 16)
 
+    // Steps LJ .. 15; returns the first column left out, one whose squares do not fit the range of doubles.
     template <int LJ>
-    __device__ __forceinline__ void step() {
+    __device__ __forceinline__ int step() {
         if constexpr (LJ < 16) {
             constexpr int par = LJ & 1, le = LJ >> 2;
-            if (LJ >= nref) return;   // uniform
+            if (LJ >= nref) return 16;   // uniform
             const bool owner = 16 * w == row0 && gq == (LJ & 3);   // lanes holding the pivot row
             if (owner) prow[par][li] = x[0][le];
             double y0[4];   // the pivot column of the first row tile, zero down to the pivot
@@ -113,7 +112,7 @@ struct QrrTile {
             };
             const double sq = total(LJ), al = prow[par][LJ], ta = total(li), pa = prow[par][li];
             double be, up, tq;
-            hh_unnormalised(al, sq, be, up, tq);
+            if (!hh_unnormalised(al, sq, be, up, tq)) return LJ;
             const double f = li > LJ ? tq * fma(up, pa, ta) : 0.0;
             if (threadIdx.x == 0) {
                 rd[LJ] = be;
@@ -129,7 +128,79 @@ struct QrrTile {
                     x[t][e] = fma(-f, row_bcast<LJ>(t == 0 ? y0[e] : x[t][e]), x[t][e]);
                 }
             if (owner) x[0][le] = li == LJ ? up : fma(-f, up, x[0][le]);
-            step<LJ + 1>();
+            return step<LJ + 1>();
+        }
+        return 16;
+    }
+
+    // The columns j0 .. nref - 1 at any scale: u is brought to order one by a power of two.  One rolled
+    // loop, with the column in LDS: handled inside the unrolled steps it cost 1 % of a 16x16 D = 6
+    // amplitude, in code alone.
+    __device__ __forceinline__ void steps_scaled(int j0, double* col) {
+        col += 16 * w + gq;   // entry (t, e) of this lane's column at 16 NW t + 4 e
+#pragma clang loop unroll(disable)
+        for (int j = j0; j < nref; ++j) {
+            const int le = j >> 2, pivot = row0 + j - 16 * w - gq;   // entry e of tile 0 is below it for 4 e > pivot
+            const bool owner = 16 * w == row0 && gq == (j & 3);
+            double mx = 0.0;   // the largest entry of the column
+            if (li == j) {
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) mx = t > 0 || 4 * e >= pivot ? fmax(mx, fabs(x[t][e])) : mx;
+            }
+            for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (owner && e == le) prow[0][li] = x[0][e];
+            if (li == 0 && gq == 0) red[0][w][0] = mx;
+            __syncthreads();
+            for (int v = 0; v < NW; ++v) mx = fmax(mx, red[0][v][0]);
+            const int ex = mx > 0.0 && mx < INFINITY ? -__builtin_amdgcn_frexp_exp(mx) : 0;
+            if (li == j) {
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool below = t > 0 || 4 * e > pivot;
+                        x[t][e] = __builtin_amdgcn_ldexp(x[t][e], below ? ex : 0);
+                        col[16 * NW * t + 4 * e] = below ? x[t][e] : 0.0;
+                    }
+            }
+            __syncthreads();
+            double s = 0.0;
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s = fma(col[16 * NW * t + 4 * e], x[t][e], s);
+                asm volatile("" : "+v"(s)::"memory");   // one tile's reads at a time
+            }
+            s = add_xor32(add_xor16(s));
+            if (gq == 0) red[1][w][li] = s;
+            __syncthreads();
+            double sq = 0.0, ta = 0.0;
+            for (int v = 0; v < NW; ++v) {
+                sq += red[1][v][j];
+                ta += red[1][v][li];
+            }
+            const double al = __builtin_amdgcn_ldexp(prow[0][j], ex);
+            const double nrm = sqrt(fma(al, al, sq)), up = sq == 0.0 ? 0.0 : al + copysign(nrm, al);
+            const double tq = sq == 0.0 ? 0.0 : 1.0 / (nrm * (nrm + fabs(al)));
+            const double f = li > j ? tq * fma(up, prow[0][li], ta) : 0.0;
+            if (threadIdx.x == 0) {
+                rd[j] = sq == 0.0 ? prow[0][j] : __builtin_amdgcn_ldexp(-copysign(nrm, al), -ex);
+                tp[j] = tq;
+            }
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x[t][e] = fma(-f, col[16 * NW * t + 4 * e], x[t][e]);
+                    if (t == 0 && owner && e == le) x[0][e] = li == j ? up : fma(-f, up, x[0][e]);
+                }
+                asm volatile("" ::: "memory");
+            }
         }
     }
 };
@@ -171,7 +242,6 @@ __global__ __launch_bounds__(64 * kQrrNW) void k_qrr_panel(QrrArgs q, int k0) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) part[w * 256 + (gq + 4 * e) * 16 + li] = acc[e];
     };
-    int ex = k0 == 0 ? 0 : (int)Tb[1024];   // exponent taken out of R
     // the tiles in turn, through the same code: the first one's reflectors reach the second as a
     // WY update on the matrix cores, and only one tile is held in registers
     const auto load_tile = [&](int c) {
@@ -235,17 +305,13 @@ __global__ __launch_bounds__(64 * kQrrNW) void k_qrr_panel(QrrArgs q, int k0) {
                 }
             }
         }
-        p.template step<0>();
+        if (const int j = p.template step<0>(); j < 16) p.steps_scaled(j, part);   // uniform
         __syncthreads();
-        if (k0 == 0 && c == 0) ex = rd[0] != 0.0 && !q.keep_scale ? -__builtin_amdgcn_frexp_exp(rd[0]) : 0;
         // the tile's part of the rows k0 .. of R, then zeros above the pivots of U
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int i = 16 * w + gq + 4 * e;   // inside the panel (t = 0)
-            if (i < nref && col < nc) {
-                const double v = col > i ? x[0][e] : (col == i ? rd[li] : 0.0);
-                Rk[(long long)i * n + k0 + col] = __builtin_amdgcn_ldexp(v, ex);
-            }
+            if (i < nref && col < nc) Rk[(long long)i * n + k0 + col] = col > i ? x[0][e] : (col == i ? rd[li] : 0.0);
             if (i < col) x[0][e] = 0.0;
         }
         if (li >= tref) {
@@ -321,7 +387,6 @@ __global__ __launch_bounds__(64 * kQrrNW) void k_qrr_panel(QrrArgs q, int k0) {
     for (int e = tid; e < nref * k0; e += 64 * NW) Rk[(long long)(e / k0) * n + e % k0] = 0.0;   // left of the panel
     if (CT == 2 && nref > 16)   // rows of the second tile, columns of the first
         for (int e = tid; e < (nref - 16) * 16; e += 64 * NW) Rk[(long long)(16 + e / 16) * n + k0 + e % 16] = 0.0;
-    if (k0 == 0 && tid == 0) Tb[1024] = (double)ex;
     if (k0 + nc >= n) return;   // no trailing column
     const int a = (tid >> 4) & 15, c = tid & 15;
     if constexpr (CT == 1) {
@@ -426,7 +491,6 @@ __global__ __launch_bounds__(64 * kQrrNW) void k_qrr_update(QrrArgs q, int k0, i
         for (int e = 0; e < 4; ++e) W2[(16 * a + gq + 4 * e) * LW + 16 * c + li] = acc[e];
     }
     __syncthreads();
-    const int ex = (int)Tb[1024];
     // step s takes the reflectors 4 gq + s: a lane reads four consecutive ones of its row
     const auto load_u = [&](int t, double (&v)[CT][4]) {
         const int tt = w + NW * t < nt ? NW * t : 0;
@@ -463,7 +527,7 @@ __global__ __launch_bounds__(64 * kQrrNW) void k_qrr_update(QrrArgs q, int k0, i
 #pragma unroll
                 for (int c = 0; c < CT; ++c)
                     if (c0 + 16 * c + li < n)
-                        row[c0 + 16 * c + li] = fin ? __builtin_amdgcn_ldexp(acc[c][e], ex) : acc[c][e];
+                        row[c0 + 16 * c + li] = acc[c][e];
             }
         }
         if (t + 1 < RT) {
@@ -517,10 +581,10 @@ int qrr_blocks(int m) { return m <= kQrrRows1 ? 1 : (m + kQrrRows1 - 1) / kQrrRo
 
 }  // namespace
 
-// one packed panel and one T (with the exponent of R behind it) per row block
+// one packed panel and one T per row block
 long long qrr_scratch_doubles(int m) {
     const int s = qrr_blocks(m), mb = std::min(m, kQrrRows1);
-    return s * ((long long)((mb + 15) / 16) * 512 + 1040);
+    return s * ((long long)((mb + 15) / 16) * 512 + 1024);
 }
 
 bool qrr_fits(int m, int n) {
@@ -540,7 +604,7 @@ hipError_t launch_qr_r(double* X, long long xs, int m, int n, double* R, long lo
     q.X = X; q.xs = xs; q.n = n; q.m = m;
     q.V = W; q.vs = ws;
     q.ot = (long long)((std::min(m, kQrrRows1) + 15) / 16) * 512;
-    q.vsub = q.ot + 1040;
+    q.vsub = q.ot + 1024;
     if (s == 1) {
         q.mb = m;
         q.nsub = 1;
@@ -553,7 +617,6 @@ hipError_t launch_qr_r(double* X, long long xs, int m, int n, double* R, long lo
     q.nsub = s;
     q.R = X; q.rs = xs; q.rsub = (long long)q.mb * n;
     q.nmat = batch * s;
-    q.keep_scale = 1;
     hipError_t e = qrr_run<false>(q, st);
     if (e != hipSuccess) return e;
     QrrArgs p = q;
@@ -562,7 +625,6 @@ hipError_t launch_qr_r(double* X, long long xs, int m, int n, double* R, long lo
     p.nsub = 1;
     p.R = R; p.rs = rs; p.rsub = 0;
     p.nmat = batch;
-    p.keep_scale = 0;
     return qrr_run<true>(p, st);
 }
 

@@ -51,6 +51,18 @@ __host__ __device__ inline TruncLayout trunc_layout(int mp, int np, int Dc) {
     return L;
 }
 
+// The exponent that brings a Gram matrix with largest diagonal entry mx to order one, 0 while the
+// squares of its entries stay in range by themselves.  A power of two moves no mantissa, and only
+// ratios of the eigenvalues are used, so M may hold entries up to 1e154, or none above 1e-154.
+__device__ __forceinline__ int gram_exponent(double mx) {
+    const bool far = mx > 0x1p400 || (mx > 0.0 && mx < 0x1p-400);
+    return far && mx < INFINITY ? -__builtin_amdgcn_frexp_exp(mx) : 0;
+}
+__device__ __forceinline__ double wave_max(double x) {
+    for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
+    return x;
+}
+
 // ---------------------------------------------------------------------------
 // tridiagonalisation in registers
 // ---------------------------------------------------------------------------
@@ -196,6 +208,8 @@ __global__ __launch_bounds__(GR * GC) void k_tr_tridiag(TruncArgs a) {
     t.ti = threadIdx.x / GC;
     t.tj = threadIdx.x % GC;
     const int ns = L.ns;
+    static_assert(GR * GC >= T::W, "a diagonal entry per thread");
+    const double dg = ld_or0((int)threadIdx.x < ns, t.Am, threadIdx.x * (L.lda + 1));
 #pragma unroll
     for (int u = 0; u < NR; ++u) {
 #pragma unroll
@@ -205,7 +219,18 @@ __global__ __launch_bounds__(GR * GC) void k_tr_tridiag(TruncArgs a) {
         }
         asm volatile("" ::: "memory");   // one row's addresses and masks at a time
     }
+    const double wm = wave_max(dg);
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = wm;
     __syncthreads();   // the rows of Am are overwritten by the reflectors
+    double mx = s_red[0];
+#pragma unroll
+    for (int i = 1; i < T::NW; ++i) mx = fmax(mx, s_red[i]);
+    if (const int ex = gram_exponent(mx)) {   // uniform
+#pragma unroll
+        for (int u = 0; u < NR; ++u)
+#pragma unroll
+            for (int w = 0; w < NC; ++w) t.A[u][w] = __builtin_amdgcn_ldexp(t.A[u][w], ex);
+    }
     if (ns > 2 && t.ti == 0) t.template pivot<0, 0>(0);
     __syncthreads();
     t.template phase<0>();
@@ -253,6 +278,15 @@ __global__ __launch_bounds__(1024) void k_tr_tridiag_mem(TruncArgs a) {
         __syncthreads();
         return s;
     };
+    const double dg = wave_max(ld_or0(tid < n, A, (long long)tid * (lda + 1)));
+    if (lane == 0) red[w] = dg;
+    __syncthreads();
+    double mx = red[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmax(mx, red[i]);
+    if (const int ex = gram_exponent(mx))   // uniform; lda = n
+        for (int i = tid; i < n * n; i += 1024) A[i] = __builtin_amdgcn_ldexp(A[i], ex);
+    __syncthreads();
     for (int k0 = 0; k0 < n - 2; k0 += kMemB) {
         const int nb = min(kMemB, n - 2 - k0);
         for (int q = 0; q < nb; ++q) {

@@ -60,8 +60,7 @@ hipError_t launch_eig(const double* V, long long vs, const double* tau, long lon
                       double* Gout, long long gos, double* scratch, long long ss, int batch,
                       hipStream_t st, const double* wyT = nullptr, long long wys = 0);
 
-// R (r x n row-major, zeros below the diagonal, r = min(m, n), scaled by a power of two) of row-major
-// m x n matrices in float64 (k_qrr.hip); X is overwritten.  W: qrr_scratch_doubles(m) doubles per
+// R (r x n row-major, zeros below the diagonal, r = min(m, n)) of row-major m x n matrices in float64 (k_qrr.hip); X is overwritten.  W: qrr_scratch_doubles(m) doubles per
 // matrix (stride ws).
 bool qrr_fits(int m, int n);
 long long qrr_scratch_doubles(int m);

@@ -178,3 +178,34 @@ def test_long_partials(case):
         assert abs(la[b] - la_o) <= 1e-10 * max(1.0, abs(la_o))
         assert abs(e[b] - e_o) <= 1e-9 * max(1.0, abs(e_o))
         assert np.linalg.norm(g[b] - d_o) <= 1e-9 * np.linalg.norm(d_o)
+
+
+# ln|W| is exact under scalings of the site tensors, far beyond the squares of doubles: a leading
+# bond index between two columns made negligible (zero, or `s` of the others) or carried by its
+# neighbour (s on one side, 1 / s on the other: the state is unchanged), the left half of the lattice
+# s per site against 1 / s in the right, and all sites small.  Column tensors with R by register
+# panels, R from the small kernels, and centres tridiagonalised in memory (order 320).
+@pytest.mark.parametrize("shape", [(6, 5, 6, 36), (6, 5, 4, 16), (6, 4, 8, 40)])
+@pytest.mark.parametrize("kind,s", [("drop", 0.0), ("drop", 1e-40), ("drop", 1e-100), ("carry", 1e-40),
+                                    ("carry", 1e-100), ("carry", 1e-150), ("halves", 1e-30), ("all", 1e-20)])
+def test_scaled_site_tensors(shape, kind, s):
+    Lx, Ly, D, Dc = shape
+    lat = Lattice(Lx, Ly, D, Dc)
+    A, S = make_random(lat, 1, 990 + D)
+    A = A.reshape(Ly, Lx, 2, D, D, D, D)   # legs left, up, right, down
+    B, shift = A.copy(), 0.0
+    if kind in ("drop", "carry"):
+        B[:, 2, :, :, :, 0] *= s
+        if kind == "carry":
+            B[:, 3, :, 0] *= 1.0 / s
+    elif kind == "halves":
+        B[:, :Lx // 2] *= s
+        B[:, Lx // 2:] *= 1.0 / s
+    else:
+        B *= s
+        shift = lat.N * np.log(s)
+    A, B = (x.reshape(lat.N, 2, D, D, D, D) for x in (A, B))
+    la, sg, fl = (t.cpu().numpy() for t in _peps().log_amplitude(*_dev(B, S), lat, "f64"))
+    la_o, sg_o, fl_o = O.log_amplitude_one(B if kind == "drop" else A, lat, S[0])
+    assert fl_o == 0 and fl[0] == 0 and int(sg[0]) == int(sg_o)
+    assert abs(la[0] - shift - la_o) <= 1e-10 * max(1.0, abs(la_o), abs(shift)), (la[0], shift, la_o)

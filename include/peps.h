@@ -298,8 +298,10 @@ peps_status peps_eval_jobs(peps_ctx* ctx, const peps_job* jobs, int32_t njobs,
 peps_status peps_autotune(peps_ctx* ctx, const peps_lattice* lat, peps_precision prec,
                           const double* A, const int8_t* S, int64_t batch, int32_t* tuned);
 
-/* Save / load the tile table as text lines "M,N,K,batch,arith,f32mask tile" (f32mask: bit 0/1/2
-   set when operand A/B/C is a float32 temporary).  Loading adds or replaces entries; tile 0
+/* Save / load the tile table as text lines "M,N,K,batch,arith,mask tile" (mask: bit 0/1/2 set
+   when operand A/B/C is a float32 temporary, bit 3 when a float64 operand is scattered, neither of
+   its indices with unit stride; such a product takes the entry without bit 3 where it has none
+   of its own).  Loading adds or replaces entries; tile 0
    selects the built-in heuristic for that shape, and numbers past the last tile are ignored. */
 peps_status peps_tune_save(peps_ctx* ctx, const char* path);
 peps_status peps_tune_load(peps_ctx* ctx, const char* path);

@@ -232,6 +232,14 @@ bool scattered(const Idx2& free, int n, const Idx2& k, int nk, int other) {
     return other > 64 && inner(free, n) >= 8 && stride(free) > 1 && inner(k, nk) >= 8 && stride(k) > 1;
 }
 
+}  // namespace
+
+bool gemm_scattered(const GemmArgs& g) {
+    return scattered(g.am, g.M, g.ak, g.K, g.N) || scattered(g.bn, g.N, g.bk, g.K, g.M);
+}
+
+namespace {
+
 // Samples a multiple of 32 KB apart: runs of tiles by XCD would start on the same memory channel
 // (D = 16, bond 32, 16 samples: a product of 328 us takes 1226).  Elsewhere runs by XCD gain up to a
 // fifth (216 x 216 x 36, 256 samples 33 us, 40 in turn).
@@ -239,7 +247,7 @@ bool camps(long long bs) { return bs != 0 && bs % 4096 == 0; }
 
 bool make_args(const GemmArgs& g, DgArgs& d) {
     if (g.a_f32 || g.b_f32 || g.c_f32 || g.beta != 0.0 || g.K <= 0) return false;
-    if (scattered(g.am, g.M, g.ak, g.K, g.N) || scattered(g.bn, g.N, g.bk, g.K, g.M)) return false;
+    if (gemm_scattered(g)) return false;
     long long ba = 0, bb = 0, bc = 0;
     // rows are mapped up to the end of their tile on the output side (masked there)
     if (!make_map(g.am, g.M, d.am, ba) || !make_map(g.bn, g.N, d.bn, bb) || !make_map(g.cm, g.M, d.cm, bc) ||

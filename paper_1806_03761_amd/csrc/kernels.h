@@ -17,10 +17,12 @@ hipError_t launch_gemm(const GemmArgs& g, Arith ar, hipStream_t st, int tile = 0
 // the same product with the roles of A and B (and of M and N) exchanged: C^T = B^T A^T
 GemmArgs gemm_transposed(const GemmArgs& g);
 // matrix-core GEMM (k_mgemm.hip): tile 1..kMfmaTiles, 0 = heuristic
-// float64 products from registers (k_dgemm.hip); done = false, nothing launched, where float32 storage,
-// beta or offsets beyond 32 bits need k_mgemm
-hipError_t launch_dgemm(const GemmArgs& g, hipStream_t st, bool& done);
 hipError_t launch_mgemm(const GemmArgs& g, Arith ar, hipStream_t st, int tile = 0);
+// float64 products from registers (k_dgemm.hip); done = false, nothing launched, where float32 storage,
+// beta, negative strides, offsets beyond 32 bits or scattered operands need k_mgemm
+hipError_t launch_dgemm(const GemmArgs& g, hipStream_t st, bool& done);
+// an operand whose every load falls on a line of its own: the register kernel leaves it to k_mgemm
+bool gemm_scattered(const GemmArgs& g);
 size_t get_lds_cap();
 
 // column-group QR with TPC lanes per column group in WG-thread workgroups; false when the

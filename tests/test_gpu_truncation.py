@@ -239,3 +239,34 @@ def test_amplitude_noise_over_many_configurations():
     d = np.abs(lb - np.log(f).sum() - la)
     assert not fl.any() and not fb.any()
     assert np.median(d) <= 1e-9 and np.mean(d > 1e-6) <= 0.01, (np.median(d), np.sort(d)[-8:])
+
+
+# products of one size whose operands are scattered or not (backward and forward site products at
+# legs of 16) are timed apart, and a table saved without the distinction still serves both
+def test_tuning_tells_scattered_products_apart(tmp_path):
+    p, lat = _peps(), Lattice(4, 4, 16, 12)
+    A, S = make_random(lat, 2, 316)
+    Ad, Sd = _dev(A, S)
+    keys, saved, path = [], str(tmp_path / "saved.txt"), str(tmp_path / "t.txt")
+
+    def load(table):
+        with open(path, "w") as f:
+            f.writelines(f"{k} {t}\n" for k, t in table.items())
+        p.tune_load(path)
+
+    p.tune_save(saved)
+    base = [t.cpu().numpy() for t in p.evaluate(Ad, Sd, lat, "f64", grad_mode=3)]
+    try:
+        p.autotune(Ad, Sd, lat, "f64")
+        p.tune_save(path)
+        keys = [ln.split()[0] for ln in open(path) if ln.strip() and not ln.startswith("#")]
+        tuned = [t.cpu().numpy() for t in p.evaluate(Ad, Sd, lat, "f64", grad_mode=3)]
+        load({k: 4 for k in keys if not k.endswith(",8")})
+        plain = [t.cpu().numpy() for t in p.evaluate(Ad, Sd, lat, "f64", grad_mode=3)]
+    finally:
+        load({k: 0 for k in keys})
+        p.tune_load(saved)
+    apart = [k for k in keys if k.endswith(",8")]
+    assert apart and all(k.split(",")[4] == "0" for k in apart)
+    for x, y, z in zip(base, tuned, plain):
+        assert np.array_equal(x, y) and np.array_equal(x, z)

@@ -131,6 +131,7 @@ struct SweepBufs {
     size_t Y = 0, Xc = 0, tauc = 0, wyc = 0, S1 = 0, Fc = 0, Hc[2] = {0, 0}, tr = 0;
     std::vector<size_t> Rc;
     size_t vL = 0, vR = 0, vZ1 = 0, vZ2 = 0, vM = 0, vRf = 0, vW = 0;
+    std::vector<std::pair<size_t, size_t>> ranges;   // [begin, end) of every buffer
 };
 
 struct Layout {
@@ -333,19 +334,8 @@ public:
             if (need_L)
                 for (int i = Ly - 1; i >= 1; --i)
                     if (trL[i]) visit_tr(tL[i]);
-            sweep.Rc.assign(Lx + 1, 0);
+            sweep = SweepBufs{};
             sweep.tr_any = any;
-            if (any) {
-                sweep.Xc = L.alloc(s_Xc);
-                sweep.tauc = L.alloc(s_tauc);
-                sweep.wyc = s_wyc > 0 ? L.alloc(s_wyc) : 0;
-                for (int c = 1; c < Lx; ++c) sweep.Rc[c] = L.alloc(s_Rc[c]);
-                sweep.S1 = L.alloc(s_S1);
-                sweep.Fc = L.alloc(s_Fc);
-                sweep.Hc[0] = L.alloc(s_Hc);
-                sweep.Hc[1] = L.alloc(s_Hc);
-                sweep.tr = L.alloc(s_tr);
-            }
         }
         // variational compression: overlap environments L_c and R_c per cut c ([c][a][l],
         // bond x bond x horizontal leg), two contraction temporaries, the updated site
@@ -375,14 +365,8 @@ public:
             for (int c = 0; c <= Lx; ++c) vc_eoff[c + 1] = vc_eoff[c] + e[c];
             s_vE = vc_eoff[Lx + 1];
             sweep.vc_any = any;
-            sweep.vL = any ? L.alloc(s_vE) : 0;
-            sweep.vR = any ? L.alloc(s_vE) : 0;
-            sweep.vZ1 = any ? L.alloc(s_vZ1) : 0;
-            sweep.vZ2 = any ? L.alloc(s_vZ2) : 0;
-            sweep.vM = any ? L.alloc(s_vM) : 0;
-            sweep.vRf = any ? L.alloc(s_vRf) : 0;
-            sweep.vW = s_vW > 0 ? L.alloc(s_vW) : 0;   // factorisations beyond LDS
         }
+        alloc_sweep(L, sweep);
         o_X.resize(Lx); o_tau.resize(Lx); o_wy.assign(Lx, 0);
         for (int j = 0; j < Lx; ++j) {
             o_X[j] = L.alloc(s_X[j]);
@@ -392,7 +376,6 @@ public:
         o_vc = s_vc > 0 ? L.alloc(s_vc) : 0;
         o_wq = s_wq > 0 ? L.alloc(s_wq) : 0;
         o_R[0] = L.alloc(s_R); o_R[1] = L.alloc(s_R);
-        sweep.Y = L.alloc(s_Y);
         o_G[0] = L.alloc(s_G); o_G[1] = L.alloc(s_G);
         o_svd = s_svd ? L.alloc(s_svd) : 0;
         s_eig = 1;
@@ -478,6 +461,38 @@ public:
         o_gws = want_g ? L.alloc((4LL * N * D4 + kGradParts - 1) / kGradParts + 1, 4LL * N * D4) : 0;
     }
 
+    // The buffers of one boundary sweep (o says which kinds of row it has).
+    void alloc_sweep(Layout& a, SweepBufs& o) const {
+        o.ranges.clear();
+        auto take = [&](long long n) -> size_t {
+            const size_t at = a.alloc(n);
+            o.ranges.emplace_back(at, a.bytes);
+            return at;
+        };
+        o.Y = take(s_Y);
+        o.Rc.assign(Lx + 1, 0);
+        if (o.tr_any) {
+            o.Xc = take(s_Xc);
+            o.tauc = take(s_tauc);
+            o.wyc = s_wyc > 0 ? take(s_wyc) : 0;
+            for (int c = 1; c < Lx; ++c) o.Rc[c] = take(s_Rc[c]);
+            o.S1 = take(s_S1);
+            o.Fc = take(s_Fc);
+            o.Hc[0] = take(s_Hc);
+            o.Hc[1] = take(s_Hc);
+            o.tr = take(s_tr);
+        }
+        if (o.vc_any) {
+            o.vL = take(s_vE);
+            o.vR = take(s_vE);
+            o.vZ1 = take(s_vZ1);
+            o.vZ2 = take(s_vZ2);
+            o.vM = take(s_vM);
+            o.vRf = take(s_vRf);
+            o.vW = s_vW > 0 ? take(s_vW) : 0;   // factorisations beyond LDS
+        }
+    }
+
     // The boundary-sweep buffers once more, for the lower sweep beside the upper one, over the
     // buffers that the sandwiches use later: no memory of its own.  False where they do not
     // fit there, or where a sweep takes the float32 modes' factorisations.
@@ -487,30 +502,22 @@ public:
         Layout a;
         a.bytes = at;
         a.Bc = Bc;
-        SweepBufs& o = side_bufs;
-        o = sweep;
-        o.Y = a.alloc(s_Y);
-        if (sweep.tr_any) {
-            o.Xc = a.alloc(s_Xc);
-            o.tauc = a.alloc(s_tauc);
-            o.wyc = s_wyc > 0 ? a.alloc(s_wyc) : 0;
-            for (int c = 1; c < Lx; ++c) o.Rc[c] = a.alloc(s_Rc[c]);
-            o.S1 = a.alloc(s_S1);
-            o.Fc = a.alloc(s_Fc);
-            o.Hc[0] = a.alloc(s_Hc);
-            o.Hc[1] = a.alloc(s_Hc);
-            o.tr = a.alloc(s_tr);
-        }
-        if (sweep.vc_any) {
-            o.vL = a.alloc(s_vE);
-            o.vR = a.alloc(s_vE);
-            o.vZ1 = a.alloc(s_vZ1);
-            o.vZ2 = a.alloc(s_vZ2);
-            o.vM = a.alloc(s_vM);
-            o.vRf = a.alloc(s_vRf);
-            o.vW = s_vW > 0 ? a.alloc(s_vW) : 0;
-        }
+        side_bufs = SweepBufs{};
+        side_bufs.tr_any = sweep.tr_any;
+        side_bufs.vc_any = sweep.vc_any;
+        alloc_sweep(a, side_bufs);
+        side_begin = at;
+        side_end = L.bytes;
         return a.bytes <= L.bytes;
+    }
+    // the two sweeps' buffers have no byte in common, and the side ones lie over sandwich buffers only
+    bool side_apart() const {
+        for (const auto& x : side_bufs.ranges) {
+            if (x.first < side_begin || x.second > side_end) return false;
+            for (const auto& y : sweep.ranges)
+                if (x.first < y.second && y.first < x.second) return false;
+        }
+        return true;
     }
 
     // The stream of the lower sweep when it may run beside the upper one, else null (one after
@@ -1296,13 +1303,18 @@ public:
         };
         const bool need_L = want_eloc || want_grad;
         if (need_L) KL(launch_fill(buf(o_logL[Ly - 1]), Bn, 0.0, st));
-        if (hipStream_t side = need_L ? side_stream() : nullptr) {
+        hipStream_t side = need_L ? side_stream() : nullptr;
+        if (side || (dry && side_fits)) {   // a dry run walks the lower sweep on its own buffers
+            if (dry && !side_apart()) {
+                bounds_msg = "internal check failed: the sweeps' buffers overlap";
+                return hipErrorInvalidValue;
+            }
             // The lower sweep beside the upper one, row by row in turn: both are chains of
             // factorisations that leave most of the device idle at tens of samples.  12x12 D = 6,
             // 48 samples, the whole evaluation 412 -> 280 ms; 8x8 D = 4, 512 samples 38 -> 31 ms.
             // Joined also after an error.
-            CK(hipEventRecord(ctx->side_ev[0], st));
-            CK(hipStreamWaitEvent(side, ctx->side_ev[0], 0));
+            KL(hipEventRecord(ctx->side_ev[0], st));
+            KL(hipStreamWaitEvent(side, ctx->side_ev[0], 0));
             hipError_t e = hipSuccess;
             for (int i = 0; i + 1 < Ly && e == hipSuccess; ++i) {
                 e = boundary(true, i);
@@ -1313,8 +1325,12 @@ public:
                 std::swap(sweep, side_bufs);
                 st_ = st;
             }
-            hipError_t j = hipEventRecord(ctx->side_ev[1], side);
-            if (j == hipSuccess) j = hipStreamWaitEvent(st, ctx->side_ev[1], 0);
+            hipError_t j = hipSuccess;
+            if (!dry) {
+                j = hipEventRecord(ctx->side_ev[1], side);
+                if (j == hipSuccess) j = hipStreamWaitEvent(st, ctx->side_ev[1], 0);
+                if (j != hipSuccess) (void)hipStreamSynchronize(side);
+            }
             CK(e);
             CK(j);
         } else {
@@ -1499,6 +1515,7 @@ public:
     // buffers of one boundary sweep, and those of the sweep on the side stream
     SweepBufs sweep, side_bufs;
     bool side_fits = false;
+    size_t side_begin = 0, side_end = 0;
     long long s_Xc = 0, s_tauc = 0, s_wyc = 0, s_S1 = 0, s_Fc = 0, s_Hc = 0, s_tr = 0;
     std::vector<long long> vc_eoff;         // offset of cut c's overlap environment
     long long s_vE = 0, s_vZ1 = 0, s_vZ2 = 0, s_vM = 0, s_vRf = 0, s_vW = 0;

@@ -270,3 +270,41 @@ def test_tuning_tells_scattered_products_apart(tmp_path):
     assert apart and all(k.split(",")[4] == "0" for k in apart)
     for x, y, z in zip(base, tuned, plain):
         assert np.array_equal(x, y) and np.array_equal(x, z)
+
+
+# the lower boundary sweep beside the upper one against the two in turn on one stream (as they run
+# while launches are timed): equal bits, over several chunks, on the default stream and on another,
+# twice on each, with work of the caller before and after
+@pytest.mark.parametrize("case", [(4, 4, 2, 4, 300, 0), (7, 5, 3, 10, 37, 0), (8, 8, 4, 16, 24, 0), (5, 6, 6, 20, 9, 0),
+                                  (6, 6, 4, 16, 17, 1), (5, 5, 6, 20, 5, 2)])
+def test_sweeps_side_by_side_equal_sweeps_in_turn(case):
+    import torch
+    Lx, Ly, D, Dc, batch, sweeps = case
+    p, lat = _peps(), Lattice(Lx, Ly, D, Dc)
+    A, S = _weak(lat, batch, 700 + D, 0.3)
+    Ad, Sd = _dev(A, S)
+    other = torch.cuda.Stream()
+    limit = p.workspace_bytes(lat, max(1, batch // 3))
+
+    def call():
+        return [t.clone() for m in (1, 3) for t in p.evaluate(Ad * 1.0, Sd, lat, "f64", grad_mode=m)]
+
+    p.set_truncation(sweeps)
+    p.set_workspace_limit(limit)
+    try:
+        p.profile_enable(("qr",))
+        turn = call()
+        p.profile_enable(())
+        got = [call(), call()]
+        torch.cuda.synchronize()
+        with torch.cuda.stream(other):
+            got += [call(), call()]
+        other.synchronize()
+    finally:
+        p.profile_enable(())
+        p.set_workspace_limit(0)
+        p.set_truncation(0)
+    assert not turn[4].any()
+    for g in got:
+        for x, y in zip(g, turn):
+            assert torch.equal(x, y)

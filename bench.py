@@ -106,8 +106,16 @@ CLASSES = ("gemm", "fused", "qr", "svd")
 CLASS_NAMES = {"svd": "truncation step (Gram matrix, tridiagonalisation, bisection, "
                       "eigenvectors, subspace refinement)",
                "qr": "Householder QR (register panels, updates on the matrix cores)",
-               "gemm": "k_dgemm contraction GEMMs (apply, sandwiches, environments)",
-               "fused": "fused sandwich steps (k_pair_mfma / k_row_step, k_step64)"}
+               "gemm": "contraction GEMMs (apply, sandwiches, environments)",
+               "fused": "fused sandwich steps"}
+# the kernels of the contraction classes: float64 products run from registers, unless the tuner
+# took another tile or an operand is scattered (legs of 8 and more)
+CLASS_KERNELS = {("gemm", "f64"): "k_dgemm, k_mgemm, k_gemm_rows", ("gemm", "f32"): "k_mgemm, k_gemm_rows",
+                 ("fused", "f64"): "k_step64", ("fused", "f32"): "k_pair_mfma, k_row_step"}
+
+
+def _kernel_name(cls, prec):
+    return f"{CLASS_NAMES[cls]}: {CLASS_KERNELS[cls, 'f64' if prec == 'f64' else 'f32']}"
 
 
 def _read(peps, classes):
@@ -119,6 +127,18 @@ def _read(peps, classes):
                     "tflops": fl / max(kms, 1e-12) / 1e9, "flops": fl, "bytes": by,
                     "gbps": by / max(kms, 1e-12) / 1e6}
     return out
+
+
+def _profiled(peps, torch, step):
+    """The class times of one untimed step (events around every launch, one stream)."""
+    torch.cuda.synchronize()
+    peps.profile_enable(CLASSES)
+    try:
+        step()
+        torch.cuda.synchronize()
+        return _read(peps, CLASSES)
+    finally:
+        peps.profile_enable(())
 
 
 HBM_PEAK_GBPS = 8000.0
@@ -288,9 +308,9 @@ def main():
     # progress lines in the timed region only for slow steps (the host runs ahead of the
     # GPU, so a line marks an enqueue, not a completion; it adds no synchronisation)
     dt_step_log = 1 if kern and sum(v["ms_total"] for v in kern.values()) > 2000 * max(args.warmup, 1) else 0
-    # timed region: only the dominant class is bracketed by events (on the library's
-    # stream), which keeps the instrumentation out of the throughput
-    peps.profile_enable((dom,))
+    # timed region: no kernel class is bracketed by events, which would also run the two
+    # boundary sweeps of an evaluation in turn instead of side by side
+    peps.profile_enable(())
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for k in range(args.steps):
@@ -300,6 +320,10 @@ def main():
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
     _log(f"timed region {dt:.1f} s")
+    # the dominant class by itself, in one more step
+    peps.profile_enable((dom,))
+    step()
+    torch.cuda.synchronize()
     timed = _read(peps, (dom,))[dom]
     peps.profile_enable(())
     ms = dt * 1e3 / args.steps
@@ -331,7 +355,7 @@ def main():
     traffic = None
     if TRAFFIC["sources"] == _sources_hash():
         traffic = TRAFFIC["bytes_per_launch"].get((name, args.prec, B, dom))
-    res["roofline"] = dict({"kernel": CLASS_NAMES[dom], "class": dom}, **_roofline(timed, peak),
+    res["roofline"] = dict({"kernel": _kernel_name(dom, args.prec), "class": dom}, **_roofline(timed, peak),
                            traffic=traffic, avg_launch_us=timed["avg_us"], launches=timed["launches"],
                            share_of_kernel_time=kern[dom]["ms_total"] / max(sum(v["ms_total"] for v in kern.values()), 1e-9))
     # every class against the dtype's matrix-core peak (the factorisations against fp64)
@@ -353,15 +377,11 @@ def main():
                 gv = torch.empty_like(grad)
                 if not args.no_tune:
                     peps.autotune(Ad, Sd, lat, args.prec)
-                step(out=gv)
-                torch.cuda.synchronize()
-                peps.profile_enable(CLASSES)
+                kv = _profiled(peps, torch, lambda: step(out=gv))
                 t1 = time.perf_counter()
                 rv = step(out=gv)
                 torch.cuda.synchronize()
                 dv = time.perf_counter() - t1
-                kv = _read(peps, CLASSES)
-                peps.profile_enable(())
             finally:
                 peps.set_truncation(0)
             lav, sgv, ev, ggv, flv = (t.detach().cpu().numpy() for t in rv)
@@ -382,15 +402,11 @@ def main():
             g6 = torch.empty((lat6.N, 2, lat6.D ** 4), dtype=torch.float64, device=dev)
             peps.set_truncation(1)
             try:
-                step("f64", A6d, S6d, lat6, g6)
-                torch.cuda.synchronize()
-                peps.profile_enable(CLASSES)
+                k6 = _profiled(peps, torch, lambda: step("f64", A6d, S6d, lat6, g6))
                 t1 = time.perf_counter()
                 r6 = step("f64", A6d, S6d, lat6, g6)
                 torch.cuda.synchronize()
                 d6 = time.perf_counter() - t1
-                k6 = _read(peps, CLASSES)
-                peps.profile_enable(())
             finally:
                 peps.set_truncation(0)
             legs["24x24_D8_Dc64_variational_1sweep"] = {
@@ -410,15 +426,11 @@ def main():
             g5 = torch.empty((lat5.N, 2, lat5.D ** 4), dtype=torch.float64, device=dev)
             peps.set_truncation(1)
             try:
-                step("f64", A5d, S5d, lat5, g5)
-                torch.cuda.synchronize()
-                peps.profile_enable(CLASSES)
+                k5 = _profiled(peps, torch, lambda: step("f64", A5d, S5d, lat5, g5))
                 t1 = time.perf_counter()
                 r5 = step("f64", A5d, S5d, lat5, g5)
                 torch.cuda.synchronize()
                 d5 = time.perf_counter() - t1
-                k5 = _read(peps, CLASSES)
-                peps.profile_enable(())
             finally:
                 peps.set_truncation(0)
             legs["16x16_D16_Dc32_variational_1sweep"] = {

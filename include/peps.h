@@ -316,7 +316,9 @@ enum { PEPS_KC_GEMM = 0, PEPS_KC_QR = 1, PEPS_KC_SVD = 2, PEPS_KC_FUSED = 3 };
  * thin QR of the variational compression 4 m n^2 - 4 n^3 / 3 (factor and explicit Q);
  * truncation step: implicit-Q apply 4 t (mz r - r^2/2) plus a thin SVD
  * min(14 a b^2 + 8 b^3, 6 a b^2 + 20 b^3) plus U_t Sigma_t 2 m n t).  Clears earlier
- * records; 0 turns timing off. */
+ * records; 0 turns timing off.  While any class is timed, the two boundary sweeps of a float64
+ * evaluation run in turn on the context's stream instead of side by side on two: the launches
+ * and results are the same, the call takes longer. */
 peps_status peps_profile_enable(peps_ctx* ctx, uint32_t class_mask);
 
 /* Synchronise the context's stream and report, for one kernel class, the summed

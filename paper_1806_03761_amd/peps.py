@@ -169,7 +169,8 @@ KERNEL_CLASS = {"gemm": 0, "qr": 1, "svd": 2, "fused": 3}
 
 def profile_enable(classes=(), device: int = 0):
     """Time every launch of the given kernel classes ("gemm", "qr", "svd", "fused") with HIP
-    events on the context's stream; () turns timing off."""
+    events on the context's stream; () turns timing off.  Timing also keeps the two boundary
+    sweeps of a float64 evaluation in turn on one stream."""
     lib, ctx = _context(device)
     mask = 0
     for c in classes:

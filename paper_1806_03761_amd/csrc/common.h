@@ -65,6 +65,21 @@ __device__ __forceinline__ T ld_or0(bool ok, const T* p, long long off) {
     return ok ? v : T(0);
 }
 
+// a reproducible scatter of bits (the start vectors of the inverse iterations)
+__device__ inline unsigned hash_u32(unsigned x) {
+    x ^= x >> 16; x *= 0x7feb352dU; x ^= x >> 15; x *= 0x846ca68bU; x ^= x >> 16;
+    return x;
+}
+
+// 1/q by the hardware reciprocal estimate refined with one Newton-Raphson step
+// (r <- r + r (1 - q r)), which roughly doubles the estimate's correct bits.  For the Sturm
+// recurrence in pivots, whose sign count is backward stable to such rounding, and for the
+// pivots of inverse iteration (bounded away from zero there), which corrects itself.
+__device__ inline double sturm_rcp(double q) {
+    const double r = __builtin_amdgcn_rcp(q);
+    return fma(fma(-q, r, 1.0), r, r);
+}
+
 // dst[i] = src[i] for i in [0, n), by threads tid, tid + nth, ...: each thread issues its
 // loads in groups of 8 before storing them, instead of a load, wait and store per
 // element (a strided loop of unknown trip count is not unrolled by the compiler).

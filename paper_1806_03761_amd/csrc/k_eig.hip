@@ -795,20 +795,6 @@ __global__ __launch_bounds__(NT) void k_eig_prep(EigArgs a) {
 // ---------------------------------------------------------------------------
 // B: eigenvalues and tridiagonal eigenvectors, one lane each
 // ---------------------------------------------------------------------------
-__device__ inline unsigned hash_u32(unsigned x) {
-    x ^= x >> 16; x *= 0x7feb352dU; x ^= x >> 15; x *= 0x846ca68bU; x ^= x >> 16;
-    return x;
-}
-
-// 1/q by the hardware reciprocal estimate refined with one Newton-Raphson step
-// (r <- r + r (1 - q r)), which roughly doubles the estimate's correct bits.  Used in the
-// Sturm recurrence, whose sign count is backward stable to such rounding, and for the
-// pivots of inverse iteration (bounded away from zero there), which corrects itself.
-__device__ inline double sturm_rcp(double q) {
-    const double r = __builtin_amdgcn_rcp(q);
-    return fma(fma(-q, r, 1.0), r, r);
-}
-
 // Block = mats_per_block matrices x tk eigenvalues x S sub-lanes.  The S sub-lanes of an
 // eigenvalue (aligned, consecutive lanes) evaluate the Sturm count at S interior points
 // of the common interval, which therefore shrinks by S + 1 per step (multisection); all

@@ -33,7 +33,7 @@ typedef double d4v __attribute__((ext_vector_type(4)));
 
 struct TruncLayout {
     int ns, tk, gram_right, lda, ldx;
-    long long oM, oA, oD, oE, oT, oX, oL, oY, oV, total;
+    long long oM, oA, oD, oE, oT, oX, oL, oY, total;
 };
 
 __host__ __device__ inline TruncLayout trunc_layout(int mp, int np, int Dc) {
@@ -50,9 +50,8 @@ __host__ __device__ inline TruncLayout trunc_layout(int mp, int np, int Dc) {
     L.oT = L.oE + L.ns;
     L.oX = L.oT + L.ns;
     L.oL = L.oX + (long long)L.ldx * L.tk;
-    L.oY = (L.oL + L.tk + 1) / 2 * 2;        // mp x tk block of the refinement; before it, with oV,
-    L.oV = L.oY + (long long)mp * L.tk;      // the iterates and pivots of k_eig_tri where they do
-    L.total = (L.oV + (long long)(np + 32) * L.tk + 1) / 2 * 2;   // not fit LDS (2 tk padded rows)
+    L.oY = L.oL + L.tk;                      // mp x tk block of the refinement
+    L.total = L.oY + (long long)mp * L.tk;
     return L;
 }
 
@@ -401,19 +400,6 @@ __global__ __launch_bounds__(1024) void k_tr_tridiag_mem(TruncArgs a) {
 // ---------------------------------------------------------------------------
 // eigenvalues and tridiagonal eigenvectors
 // ---------------------------------------------------------------------------
-__device__ inline unsigned hash_u32(unsigned x) {
-    x ^= x >> 16; x *= 0x7feb352dU; x ^= x >> 15; x *= 0x846ca68bU; x ^= x >> 16;
-    return x;
-}
-
-// 1/q by the hardware reciprocal estimate refined with one Newton-Raphson step
-// (r <- r + r (1 - q r)), which roughly doubles the estimate's correct bits; the pivots of the
-// inverse iteration are bounded away from zero, and it corrects itself.
-__device__ inline double sturm_rcp(double q) {
-    const double r = __builtin_amdgcn_rcp(q);
-    return fma(fma(-q, r, 1.0), r, r);
-}
-
 // Eigenvalues (PART & 1) and tridiagonal eigenvectors (PART & 2).  Block = mpb matrices x epb
 // eigenvalues x S sub-lanes (bpm blocks cover the tk eigenvalues of a matrix when mpb = 1).
 // The S sub-lanes of an eigenvalue (a power of two, so they lie in one wave) evaluate the
@@ -438,7 +424,7 @@ __device__ inline double sturm_rcp(double q) {
 static constexpr int kTriLevels = 52;   // an interval of 2^-51, about 4.5e-16 of the norm
 __host__ __device__ inline int tri_pad(int n) { return (n + 15) / 16 * 16; }
 
-template <int PART, bool LDS>
+template <int PART>
 __global__ __launch_bounds__(256) void k_eig_tri(TruncArgs a, int S, int mpb, int epb, int bpm) {
     extern __shared__ __align__(16) double tri_lds[];
     const TruncLayout L = trunc_layout(a.mp, a.np, a.Dc);
@@ -548,8 +534,8 @@ __global__ __launch_bounds__(256) void k_eig_tri(TruncArgs a, int S, int mpb, in
     }
     if constexpr ((PART & 2) != 0) {
         // the lane's iterate with its reciprocal pivots, row i of every lane side by side
-        const int xs = LDS ? nvl : tk;
-        double2* xp = LDS ? xl + mi * epb + (l - part * epb) : reinterpret_cast<double2*>(gs + L.oY) + l;
+        const int xs = nvl;
+        double2* xp = xl + mi * epb + (l - part * epb);
         // inverse iteration (T - lam I) x = b with T - lam I = L D L^T, factored once
         const double ptol = fmax(2.220446049250313e-16 * tnorm, 1e-300);
         {
@@ -663,8 +649,8 @@ __global__ __launch_bounds__(256) void k_eig_tri(TruncArgs a, int S, int mpb, in
 // only pay while waves are missing: S grows while the lanes fit 1.5 waves per SIMD (steps
 // 52 / log2 S, or 52 with one point; S = 2 would be one level on two lanes).  Wide
 // matrices are cut into blocks of 256 lanes so that they spread over the CUs, narrow ones
-// packed until a wave is full.  The iterates are in LDS where one block of them fits (16 bytes
-// per row and lane; else in the scratch).  One launch does both parts where every block
+// packed until a wave is full.  The iterates are in LDS, 16 bytes per row and lane (16 lanes of order
+// 512: 144 KB).  One launch does both parts where every block
 // stays resident with its iterates; a fuller chip takes two, so that the counts, which need
 // little LDS, keep all SIMDs busy.
 static hipError_t launch_eig_tri(const TruncArgs& a, const TruncLayout& L, size_t cap, hipStream_t st) {
@@ -697,15 +683,15 @@ static hipError_t launch_eig_tri(const TruncArgs& a, const TruncLayout& L, size_
     for (int s = 4; s <= 32; s *= 2)
         if ((long long)batch * tk * s <= 98304) S = s;
     const Shape v = shape(S);
-#define TRI(PART_, LDS_, sh, bytes_)                                                                              \
-    hipLaunchKernelGGL((k_eig_tri<PART_, LDS_>), dim3((unsigned)sh.blocks), dim3(sh.threads), (bytes_), st, a, \
+#define TRI(PART_, sh, bytes_)                                                                              \
+    hipLaunchKernelGGL((k_eig_tri<PART_>), dim3((unsigned)sh.blocks), dim3(sh.threads), (bytes_), st, a, \
                        sh.S, sh.mpb, sh.epb, sh.bpm)
     const size_t both = v.base + v.vec;
     if (both <= cap && (v.blocks + 255) / 256 <= (long long)(cap / both)) {
-        TRI(3, true, v, both);
+        TRI(3, v, both);
         return hipGetLastError();
     }
-    TRI(1, true, v, v.base);
+    TRI(1, v, v.base);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     Shape w = shape(1);
@@ -726,8 +712,8 @@ static hipError_t launch_eig_tri(const TruncArgs& a, const TruncLayout& L, size_
         w.threads = (w.epb + 63) / 64 * 64;
         w.blocks = (long long)batch * w.bpm;
     }
-    if (w.base + w.vec <= cap) TRI(2, true, w, w.base + w.vec);
-    else TRI(2, false, w, w.base);
+    if (w.base + w.vec > cap) return hipErrorInvalidValue;
+    TRI(2, w, w.base + w.vec);
 #undef TRI
     return hipGetLastError();
 }

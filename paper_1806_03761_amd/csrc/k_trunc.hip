@@ -55,16 +55,12 @@ __host__ __device__ inline TruncLayout trunc_layout(int mp, int np, int Dc) {
     return L;
 }
 
-// The exponent that brings a Gram matrix with largest diagonal entry mx to order one, 0 while the
-// squares of its entries stay in range by themselves.  A power of two moves no mantissa, and only
-// ratios of the eigenvalues are used, so M may hold entries up to 1e154, or none above 1e-154.
-__device__ __forceinline__ int gram_exponent(double mx) {
-    const bool far = mx > 0x1p400 || (mx > 0.0 && mx < 0x1p-400);
-    return far && mx < INFINITY ? -__builtin_amdgcn_frexp_exp(mx) : 0;
-}
-__device__ __forceinline__ double wave_max(double x) {
-    for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
-    return x;
+// The exponent that brings a Gram matrix of this trace to order one, 0 while the squares of its
+// entries stay in range by themselves.  A power of two moves no mantissa, and only ratios of the
+// eigenvalues are used, so M may hold entries up to 1e154, or none above 1e-154.
+__device__ __forceinline__ int gram_exponent(double trace) {
+    const bool far = trace > 0x1p400 || (trace > 0.0 && trace < 0x1p-400);
+    return far && trace < INFINITY ? -__builtin_amdgcn_frexp_exp(trace) : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -223,13 +219,15 @@ __global__ __launch_bounds__(GR * GC) void k_tr_tridiag(TruncArgs a) {
         }
         asm volatile("" ::: "memory");   // one row's addresses and masks at a time
     }
-    const double wm = wave_max(dg);
-    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = wm;
+    double trace = lane_group_sum(dg, 64);
+    if (T::NW > 1 && (threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = trace;
     __syncthreads();   // the rows of Am are overwritten by the reflectors
-    double mx = s_red[0];
+    if constexpr (T::NW > 1) {
+        trace = s_red[0];
 #pragma unroll
-    for (int i = 1; i < T::NW; ++i) mx = fmax(mx, s_red[i]);
-    if (const int ex = gram_exponent(mx)) {   // uniform
+        for (int i = 1; i < T::NW; ++i) trace += s_red[i];
+    }
+    if (const int ex = __builtin_amdgcn_readfirstlane(gram_exponent(trace))) {
 #pragma unroll
         for (int u = 0; u < NR; ++u)
 #pragma unroll
@@ -282,13 +280,8 @@ __global__ __launch_bounds__(1024) void k_tr_tridiag_mem(TruncArgs a) {
         __syncthreads();
         return s;
     };
-    const double dg = wave_max(ld_or0(tid < n, A, (long long)tid * (lda + 1)));
-    if (lane == 0) red[w] = dg;
-    __syncthreads();
-    double mx = red[0];
-#pragma unroll
-    for (int i = 1; i < 16; ++i) mx = fmax(mx, red[i]);
-    if (const int ex = gram_exponent(mx))   // uniform; lda = n
+    const double trace = block_sum(ld_or0(tid < n, A, (long long)tid * (lda + 1)));
+    if (const int ex = gram_exponent(trace))   // uniform; lda = n
         for (int i = tid; i < n * n; i += 1024) A[i] = __builtin_amdgcn_ldexp(A[i], ex);
     __syncthreads();
     for (int k0 = 0; k0 < n - 2; k0 += kMemB) {

@@ -100,9 +100,9 @@ peps_status peps_set_truncation(peps_ctx* ctx, int32_t sweeps);
 
 /* Fused sandwich steps (enable != 0, the default): the single- and two-row steps
  * of the float32 and bfloat16 modes with legs <= 4 and boundary bonds <= 16, and of the
- * float64 mode with legs <= 4 and bonds that fit the chip, run as one kernel each, summing every product in the order of the GEMM form, so their results
- * equal the GEMM form's bit for bit.  enable = 0 keeps the GEMM form (a comparison
- * switch; slower). */
+ * float64 mode with legs <= 4 and bonds that fit the chip, run as one kernel each, summing
+ * every product in the order of the GEMM form, so their results equal the GEMM form's bit
+ * for bit.  enable = 0 keeps the GEMM form (a comparison switch; slower). */
 peps_status peps_set_fused_steps(peps_ctx* ctx, int32_t enable);
 
 /* Cap the device workspace in bytes (0 = default: 1/4 of free device memory at

@@ -552,6 +552,10 @@ hipError_t qrr_step(const QrrArgs& q, int k0, hipStream_t st) {
     return hipGetLastError();
 }
 
+// The height of a panel is the number of 16-row tiles per wave (128 rows each), a launch of its own.  A
+// panel of 1024 matrices takes 104 us with one, 152 with two, 399 with nine and 538 with eleven, so a
+// spare tile costs 8 to 13 % of it.  Above 1024 rows, where a tall tensor spends most of its panels,
+// every height is there; below, where a panel is cheap and only few are left, every second one.
 template <bool MAP>
 hipError_t qrr_run(const QrrArgs& q, hipStream_t st) {
     const int rows = q.nsub > 1 ? q.mb : q.m, r = std::min(rows, q.n);

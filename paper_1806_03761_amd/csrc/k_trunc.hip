@@ -414,7 +414,8 @@ __global__ __launch_bounds__(1024) void k_tr_tridiag_mem(TruncArgs a) {
 // e = 0), the next chunk's loads in flight during the current one.  The 49 launches of an
 // 8x8, D = 4, Dc = 16 amplitude: 6.7 ms with pivots and one row at a time, 3.5 ms so (4096
 // samples), 4.2 and 1.5 ms (one sample); order 216, 256 matrices: 550 and 173 us a launch.
-static constexpr int kTriLevels = 52;   // an interval of 2^-51, about 4.5e-16 of the norm
+// an interval of 2^-51: 4.4e-16 to 8.9e-16 of the norm, which the Rayleigh quotient then leaves
+static constexpr int kTriLevels = 52;
 __host__ __device__ inline int tri_pad(int n) { return (n + 15) / 16 * 16; }
 
 template <int PART>
@@ -756,9 +757,8 @@ __device__ __forceinline__ void mat_product(const double* Mat, int ld, int nx, i
     }
 }
 
-// Columns are scaled by a power of two as they are loaded, which changes no subspace and keeps
-// their squared norms in range.
-// orthonormal basis of the m x tk block X (column-major) in place
+// Orthonormal basis of the m x tk block X (column-major) in place.  Columns are scaled by a power
+// of two as they are loaded, which changes no subspace and keeps their squared norms in range.
 template <int NW, int SL, int RPL>
 __device__ __forceinline__ void block_orth(double* X, int m, int tk, double (*vbuf)[64 * RPL], double* tau) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -791,7 +791,6 @@ __device__ __forceinline__ void block_orth(double* X, int m, int tk, double (*vb
         }
     }
 }
-
 
 // X <- H_0 ... H_{ns-3} X (the reflectors of the tridiagonalisation, row k of Am beyond k+1, unit
 // entry at k+1) in compact WY blocks of 16, on the matrix cores.  X (ns x tk at Xg, ld ldx) is
@@ -943,7 +942,8 @@ __device__ __forceinline__ void back_transform(const double* Xg, int ldx, const 
 //   Gram route alone left ln|W| of a 24 x 24, D = 8 state ten times the oracle's rounding noise
 //   away;
 //   H = F V.
-// Bound by the chain of 2 tk (with refinement up to 6 tk) reflector steps, about 0.9 us each;
+// Bound by the chain of reflector steps, 2 tk per orthonormalisation and about 0.9 us each: one of
+// them for order np, two for order mp, and two more with refinement (2, 4, 6 or 8 tk steps);
 // the blocks pass between the phases through the scratch (L2).  Order 216, tk = 36, 256 matrices
 // without refinement: 217 us, where Gram-Schmidt and one reflector at a time from memory took
 // 607 us and left the carried factor to be formed; 48 matrices with it: 385 us against 543 us
@@ -985,7 +985,12 @@ __global__ __launch_bounds__(NW * 64, SL * RPL <= 8 ? 4 : 2) void k_tr_vec(Trunc
     mat_product<NW, NC, true>(a.F + (long long)b * a.fs, np, a.nf, np, tk, V, np, a.H + (long long)b * a.hs, tk, 1);
 }
 
-// the smallest blocking of k_tr_vec that holds the blocks; false when none does
+// The smallest blocking of k_tr_vec that holds the blocks; false when none does.  NW waves of SL
+// columns and 64 RPL rows: one wave per SIMD up to 16 columns (a second one only adds to a step),
+// two for more; blocks of 64 rows that hold nothing cost every step.  (8, 5, 4) is there because 33 to 40
+// columns of up to 256 rows would else run in twice the registers and twice the rows (8, 8, 8):
+// order 216, 36 columns, truncation class of a 12x12 evaluation (48 samples) 170 ms with it, 207 ms
+// without; 16x16 amplitudes (256 samples) 164 and 187 ms.
 template <class Fn>
 bool vec_blocking(int m, int t, Fn&& fn) {
 #define VB(NW_, SL_, RPL_) \

@@ -55,12 +55,27 @@ __host__ __device__ inline TruncLayout trunc_layout(int mp, int np, int Dc) {
     return L;
 }
 
-// The exponent that brings a Gram matrix of this trace to order one, 0 while the squares of its
-// entries stay in range by themselves.  A power of two moves no mantissa, and only ratios of the
-// eigenvalues are used, so M may hold entries up to 1e154, or none above 1e-154.
-__device__ __forceinline__ int gram_exponent(double trace) {
+// A Gram matrix (n x n, n at most NT threads) scaled to a trace of order one where the squares of its
+// entries would leave the range of doubles.  A power of two moves no mantissa, and only ratios of the
+// eigenvalues are used, so M may hold entries up to 1e154, or none above 1e-154.  Done in memory
+// before the matrix is loaded: on the registers it cost them (order 216: 1.94 -> 2.08 ms a launch of
+// 1024 matrices).  red: LDS, a double per wave.
+template <int NT>
+__device__ __forceinline__ void gram_scale(double* A, int n, double* red) {
+    double trace = lane_group_sum(ld_or0((int)threadIdx.x < n, A, (int)threadIdx.x * (n + 1)), 64);
+    if constexpr (NT > 64) {
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = trace;
+        __syncthreads();
+        trace = red[0];
+#pragma unroll
+        for (int i = 1; i < NT / 64; ++i) trace += red[i];
+    }
     const bool far = trace > 0x1p400 || (trace > 0.0 && trace < 0x1p-400);
-    return far && trace < INFINITY ? -__builtin_amdgcn_frexp_exp(trace) : 0;
+    if (!__builtin_amdgcn_readfirstlane(far && trace < INFINITY)) return;
+    const int ex = -__builtin_amdgcn_frexp_exp(trace);
+    __syncthreads();
+    for (int i = threadIdx.x; i < n * n; i += NT) A[i] = __builtin_amdgcn_ldexp(A[i], ex);
+    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -209,7 +224,7 @@ __global__ __launch_bounds__(GR * GC) void k_tr_tridiag(TruncArgs a) {
     t.tj = threadIdx.x % GC;
     const int ns = L.ns;
     static_assert(GR * GC >= T::W, "a diagonal entry per thread");
-    const double dg = ld_or0((int)threadIdx.x < ns, t.Am, threadIdx.x * (L.lda + 1));
+    gram_scale<GR * GC>(t.Am, ns, s_red);
 #pragma unroll
     for (int u = 0; u < NR; ++u) {
 #pragma unroll
@@ -219,20 +234,7 @@ __global__ __launch_bounds__(GR * GC) void k_tr_tridiag(TruncArgs a) {
         }
         asm volatile("" ::: "memory");   // one row's addresses and masks at a time
     }
-    double trace = lane_group_sum(dg, 64);
-    if (T::NW > 1 && (threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = trace;
     __syncthreads();   // the rows of Am are overwritten by the reflectors
-    if constexpr (T::NW > 1) {
-        trace = s_red[0];
-#pragma unroll
-        for (int i = 1; i < T::NW; ++i) trace += s_red[i];
-    }
-    if (const int ex = __builtin_amdgcn_readfirstlane(gram_exponent(trace))) {
-#pragma unroll
-        for (int u = 0; u < NR; ++u)
-#pragma unroll
-            for (int w = 0; w < NC; ++w) t.A[u][w] = __builtin_amdgcn_ldexp(t.A[u][w], ex);
-    }
     if (ns > 2 && t.ti == 0) t.template pivot<0, 0>(0);
     __syncthreads();
     t.template phase<0>();
@@ -280,9 +282,7 @@ __global__ __launch_bounds__(1024) void k_tr_tridiag_mem(TruncArgs a) {
         __syncthreads();
         return s;
     };
-    const double trace = block_sum(ld_or0(tid < n, A, (long long)tid * (lda + 1)));
-    if (const int ex = gram_exponent(trace))   // uniform; lda = n
-        for (int i = tid; i < n * n; i += 1024) A[i] = __builtin_amdgcn_ldexp(A[i], ex);
+    gram_scale<1024>(A, n, red);
     __syncthreads();
     for (int k0 = 0; k0 < n - 2; k0 += kMemB) {
         const int nb = min(kMemB, n - 2 - k0);

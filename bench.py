@@ -82,13 +82,13 @@ def finish_cpu_baseline(h, name):
                       f"steps; wall {dt:.1f} s"}
 
 
-# HBM traffic per launch of the contraction GEMMs, from two rocprofv3 --pmc passes
+# HBM traffic per launch of a contraction class, from two rocprofv3 --pmc passes
 # (FETCH_SIZE, WRITE_SIZE, KiB per dispatch) over one evaluation, each scaled by what the
 # same counter reads for a 256 MiB device copy (FETCH_SIZE reads half of the copied bytes:
 # factor 2.0; WRITE_SIZE all: 1.0).  Valid only for the kernel sources they were measured
 # on (hash below) and the workload, arithmetic and batch named; otherwise null.
-TRAFFIC = {"sources": "d2c823b1675075b6",
-           "bytes_per_launch": {("8x8_D4_Dc16", "f64", 4096, "gemm"): 166.4e6}}
+TRAFFIC = {"sources": "f66ccebadd3b3af0",
+           "bytes_per_launch": {("8x8_D4_Dc16", "f64", 4096, "fused"): 152.0e6}}
 
 
 def _sources_hash() -> str:

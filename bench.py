@@ -87,7 +87,7 @@ def finish_cpu_baseline(h, name):
 # same counter reads for a 256 MiB device copy (FETCH_SIZE reads half of the copied bytes:
 # factor 2.0; WRITE_SIZE all: 1.0).  Valid only for the kernel sources they were measured
 # on (hash below) and the workload, arithmetic and batch named; otherwise null.
-TRAFFIC = {"sources": "f66ccebadd3b3af0",
+TRAFFIC = {"sources": "20d987755fe91aa2",
            "bytes_per_launch": {("8x8_D4_Dc16", "f64", 4096, "fused"): 152.0e6}}
 
 
